@@ -7,11 +7,13 @@
 #include <hip/hip_runtime.h>
 
 #include "sci_internal.h"
+#include "sci_math.h"
 
 namespace sci {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kProjBlock = 64; // projection: one wavefront per workgroup
 
 inline unsigned grid_for(size_t n)
 {
@@ -110,102 +112,6 @@ __global__ __launch_bounds__(kBlock) void k_project(uint32_t npix, int B, float 
     }
 }
 
-// Same projection with every frame of the pixel held in registers (KB >= B),
-// so theta, u and C are read from memory once.
-template <int MODE, int KB>
-__global__ __launch_bounds__(kBlock) void k_project_reg(uint32_t npix, int B, float ex, float a1, float a2, const float *__restrict__ w, const float *__restrict__ theta,
-                                                        const float *__restrict__ u, const float *__restrict__ C,
-                                                        const float *__restrict__ Y, const float *__restrict__ Sinv,
-                                                        float *__restrict__ x, float *__restrict__ svol)
-{
-    uint32_t pix = blockIdx.x * kBlock + threadIdx.x;
-    if (pix >= npix) return;
-    constexpr bool ADMM = MODE == kProjAdmm;
-    float v[KB], c[KB], uu[KB];
-    float acc = 0.0f;
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * npix + pix;
-            c[k] = C[o];
-            if (ADMM) {
-                uu[k] = u[o];
-                v[k] = theta[o] - uu[k];
-            } else if (MODE == kProjFista) {
-                v[k] = fista_point(theta[o], u[o], ex);
-            } else if (MODE == kProjTwist) {
-                v[k] = twist_point(u[o], theta[o], w[o], ex, a1, a2);
-            } else {
-                v[k] = theta[o];
-            }
-            acc = fmaf(c[k], v[k], acc);
-        }
-    }
-    const float r = (Y[pix] - acc) * Sinv[pix];
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * npix + pix;
-            const float xv = fmaf(c[k], r, v[k]);
-            if (!ADMM || x) x[o] = xv;
-            if (ADMM) svol[o] = uu[k] + xv;
-            if (MODE == kProjTwist) svol[o] = v[k];
-        }
-    }
-}
-
-// Two adjacent pixels per thread (8-byte loads and stores), every frame in
-// registers; the same per-pixel arithmetic as k_project_reg.
-template <int MODE, int KB>
-__global__ __launch_bounds__(kBlock) void k_project_reg2(uint32_t npair, uint32_t npix, int B, float ex, float a1, float a2, const float2 *__restrict__ w,
-                                                         const float2 *__restrict__ theta,
-                                                         const float2 *__restrict__ u, const float2 *__restrict__ C,
-                                                         const float2 *__restrict__ Y,
-                                                         const float2 *__restrict__ Sinv, float2 *__restrict__ x,
-                                                         float2 *__restrict__ svol)
-{
-    const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
-    if (q >= npair) return;
-    constexpr bool ADMM = MODE == kProjAdmm;
-    const uint32_t fstride = npix / 2; // float2 elements per frame
-    float2 v[KB], c[KB], uu[KB];
-    float acc0 = 0.0f, acc1 = 0.0f;
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * fstride + q;
-            c[k] = C[o];
-            if (ADMM) {
-                uu[k] = u[o];
-                const float2 t = theta[o];
-                v[k] = make_float2(t.x - uu[k].x, t.y - uu[k].y);
-            } else if (MODE == kProjFista) {
-                const float2 t = theta[o], tp = u[o];
-                v[k] = make_float2(fista_point(t.x, tp.x, ex), fista_point(t.y, tp.y, ex));
-            } else if (MODE == kProjTwist) {
-                const float2 t = theta[o], tp = u[o], tw = w[o];
-                v[k] = make_float2(twist_point(tp.x, t.x, tw.x, ex, a1, a2), twist_point(tp.y, t.y, tw.y, ex, a1, a2));
-            } else {
-                v[k] = theta[o];
-            }
-            acc0 = fmaf(c[k].x, v[k].x, acc0);
-            acc1 = fmaf(c[k].y, v[k].y, acc1);
-        }
-    }
-    const float2 yv = Y[q], sv = Sinv[q];
-    const float r0 = (yv.x - acc0) * sv.x, r1 = (yv.y - acc1) * sv.y;
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * fstride + q;
-            const float2 xv = make_float2(fmaf(c[k].x, r0, v[k].x), fmaf(c[k].y, r1, v[k].y));
-            if (!ADMM || x) x[o] = xv;
-            if (ADMM) svol[o] = make_float2(uu[k].x + xv.x, uu[k].y + xv.y);
-            if (MODE == kProjTwist) svol[o] = v[k];
-        }
-    }
-}
-
 // Binary masks packed one bit per frame into a 32-bit word per pixel
 // (B <= 32): bits[pix] bit k = (C_k(pix) == 1). flag (set to 1 beforehand)
 // is cleared when any entry is neither 0 nor 1; the projection then reads C.
@@ -227,96 +133,117 @@ __global__ __launch_bounds__(kBlock) void k_pack_masks(uint32_t npix, int B, con
 
 __global__ void k_set_flag(int *flag, int v) { *flag = v; }
 
-// The projection with binary masks read from the packed bits: C_k is 0 or
-// 1, so fmaf(C_k, v, acc) and fmaf(C_k, r, v) reduce exactly to a select of
-// acc + v / acc and v + r / v, the same values the float path produces. Two
-// adjacent pixels per thread; when *flag is 0 the float masks are used.
+// The projection with every frame of a pixel in registers (B <= KB <= 32), so
+// that each volume is read once. HBM stream (GAP: read theta, write x); below
+// a few million voxels its time is the latency of its loads. All of them are
+// issued before the first use: every slot k < KB loads unconditionally (a slot
+// past the last frame repeats frame B - 1 and drops out of the sum). A test of
+// k < B around each load puts the load and its use in a basic block of their
+// own, and the frames then come in one latency after another: with that, GAP
+// took 5.1 / 10.3 / 39.6 us inside a solve at 256x256x8 / 512x512x10 /
+// 1024x1024x24 (5.1 TB/s), without it 3.3 / 5.8 / 32.4 us (6.2 TB/s; back to
+// back 2.6 / 4.1 / 27.1 us). One pixel per thread and one wavefront per
+// workgroup were as fast as any other split up to 512x512x24 and faster at
+// 1024x1024x24 (256 threads 30.1 us back to back, two pixels per thread 28.4
+// to 33.0 us): the finest grain leaves the shortest last round. Workgroups are
+// numbered XCD-contiguously, so that an XCD projects the band of rows whose
+// theta the row-major denoisers (VTV) left in its L2: 8.6 -> 5.8 us at
+// 512x512x10.
+//
+// Binary masks come as packed bits (*flag != 0): C_k is 0 or 1, so
+// fmaf(C_k, v, acc) and fmaf(C_k, r, v) give the same values as with the float
+// masks, which are read where *flag is 0.
 template <int MODE, int KB>
-__global__ __launch_bounds__(kBlock) void k_project_bits(uint32_t npair, uint32_t npix, int B, float ex, float a1, float a2, const float2 *__restrict__ w,
-                                                         const float2 *__restrict__ theta,
-                                                         const float2 *__restrict__ u, const float2 *__restrict__ C,
-                                                         const uint2 *__restrict__ bits, const int *__restrict__ flag,
-                                                         const float2 *__restrict__ Y, const float2 *__restrict__ Sinv,
-                                                         float2 *__restrict__ x, float2 *__restrict__ svol)
+__global__ __launch_bounds__(kProjBlock) void k_project_reg(uint32_t npix, int B, float ex, float a1, float a2,
+                                                            const float *__restrict__ w,
+                                                            const float *__restrict__ theta,
+                                                            const float *__restrict__ u, const float *__restrict__ C,
+                                                            const uint32_t *__restrict__ bits,
+                                                            const int *__restrict__ flag,
+                                                            const float *__restrict__ Y,
+                                                            const float *__restrict__ Sinv, float *__restrict__ x,
+                                                            float *__restrict__ svol)
 {
-    const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
-    if (q >= npair) return;
+    const uint32_t pix = (uint32_t)xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * kProjBlock + threadIdx.x;
+    if (pix >= npix) return;
     constexpr bool ADMM = MODE == kProjAdmm;
-    const uint32_t fstride = npix / 2;
-    const bool packed = *flag != 0;
-    float2 v[KB], uu[KB];
-    uint2 m = packed ? bits[q] : make_uint2(0u, 0u);
-    float2 c[KB];
-    float acc0 = 0.0f, acc1 = 0.0f;
+    float v[KB], uu[KB], ww[KB];
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * fstride + q;
-            if (packed) c[k] = make_float2((m.x >> k) & 1u ? 1.0f : 0.0f, (m.y >> k) & 1u ? 1.0f : 0.0f);
-            else c[k] = C[o];
-            if (ADMM) {
-                uu[k] = u[o];
-                const float2 t = theta[o];
-                v[k] = make_float2(t.x - uu[k].x, t.y - uu[k].y);
-            } else if (MODE == kProjFista) {
-                const float2 t = theta[o], tp = u[o];
-                v[k] = make_float2(fista_point(t.x, tp.x, ex), fista_point(t.y, tp.y, ex));
-            } else if (MODE == kProjTwist) {
-                const float2 t = theta[o], tp = u[o], tw = w[o];
-                v[k] = make_float2(twist_point(tp.x, t.x, tw.x, ex, a1, a2), twist_point(tp.y, t.y, tw.y, ex, a1, a2));
-            } else {
-                v[k] = theta[o];
-            }
-            acc0 = fmaf(c[k].x, v[k].x, acc0);
-            acc1 = fmaf(c[k].y, v[k].y, acc1);
-        }
+        const uint32_t o = (uint32_t)min(k, B - 1) * npix + pix;
+        v[k] = theta[o];
+        if (MODE != kProjGap) uu[k] = u[o];
+        if (MODE == kProjTwist) ww[k] = w[o];
     }
-    const float2 yv = Y[q], sv = Sinv[q];
-    const float r0 = (yv.x - acc0) * sv.x, r1 = (yv.y - acc1) * sv.y;
+    const uint32_t m = bits[pix];
+    const float yv = Y[pix], sv = Sinv[pix];
+    // the rest, with C_k from cof(k)
+    auto finish = [&](auto cof) {
+        float acc = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {
-        if (k < B) {
-            const uint32_t o = (uint32_t)k * fstride + q;
-            const float2 xv = make_float2(fmaf(c[k].x, r0, v[k].x), fmaf(c[k].y, r1, v[k].y));
-            if (!ADMM || x) x[o] = xv;
-            if (ADMM) svol[o] = make_float2(uu[k].x + xv.x, uu[k].y + xv.y);
-            if (MODE == kProjTwist) svol[o] = v[k];
+        for (int k = 0; k < KB; ++k) {
+            if (ADMM) v[k] = v[k] - uu[k];
+            else if (MODE == kProjFista) v[k] = fista_point(v[k], uu[k], ex);
+            else if (MODE == kProjTwist) v[k] = twist_point(uu[k], v[k], ww[k], ex, a1, a2);
+            if (k < B) acc = fmaf(cof(k), v[k], acc);
         }
+        const float r = (yv - acc) * sv;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            if (k < B) {
+                const uint32_t o = (uint32_t)k * npix + pix;
+                const float xv = fmaf(cof(k), r, v[k]);
+                if (!ADMM || x) x[o] = xv;
+                if (ADMM) svol[o] = uu[k] + xv;
+                if (MODE == kProjTwist) svol[o] = v[k];
+            }
+        }
+    };
+    if (*flag != 0) { // uniform
+        finish([&](int k) { return (m >> k) & 1u ? 1.0f : 0.0f; });
+    } else {
+        float c[KB];
+#pragma unroll
+        for (int k = 0; k < KB; ++k) c[k] = C[(uint32_t)min(k, B - 1) * npix + pix];
+        finish([&](int k) { return c[k]; });
     }
 }
 
+struct ProjArgs {
+    uint32_t npix;
+    int B;
+    float ex, a1, a2;
+    const float *w, *theta, *u, *C;
+    const uint32_t *bits;
+    const int *flag;
+    const float *Y, *Sinv;
+    float *x, *svol;
+    hipStream_t s;
+};
+
+// Launch with the smallest even slot count that holds B frames.
+template <int MODE, int KB = 2> void launch_project_reg(const ProjArgs &a)
+{
+    if constexpr (KB < 32) {
+        if (a.B > KB) return launch_project_reg<MODE, KB + 2>(a);
+    }
+    hipLaunchKernelGGL((k_project_reg<MODE, KB>), dim3((a.npix + kProjBlock - 1) / kProjBlock), dim3(kProjBlock), 0, a.s,
+                       a.npix, a.B, a.ex, a.a1, a.a2, a.w, a.theta, a.u, a.C, a.bits, a.flag, a.Y, a.Sinv, a.x,
+                       a.svol);
+}
+
+// At most 32 frames, packed masks at hand (every solver has them): registers;
+// else, frames beyond the mask word, the loop over frames.
 template <int MODE>
 void launch_project(uint32_t npix, int B, float ex, const float *theta, const float *u, const float *C,
-                    const float *Y, const float *Sinv, float *x, float *svol, hipStream_t s,
-                    const uint32_t *cbits = nullptr, const int *cflag = nullptr, float a1 = 0.0f, float a2 = 0.0f,
-                    const float *w = nullptr)
+                    const float *Y, const float *Sinv, float *x, float *svol, hipStream_t s, const uint32_t *cbits,
+                    const int *cflag, float a1 = 0.0f, float a2 = 0.0f, const float *w = nullptr)
 {
-    const dim3 g(grid_for(npix)), b(kBlock);
-    auto al8 = [](const void *p) { return p == nullptr || ((uintptr_t)p & 7u) == 0; };
-    if (npix % 2 == 0 && B <= 32 && al8(theta) && al8(u) && al8(C) && al8(Y) && al8(Sinv) && al8(x) && al8(svol) && al8(w)) {
-        const uint32_t npair = npix / 2;
-        const dim3 g2(grid_for(npair));
-        const float2 *t2 = (const float2 *)theta, *u2 = (const float2 *)u, *C2 = (const float2 *)C;
-        const float2 *Y2 = (const float2 *)Y, *S2 = (const float2 *)Sinv;
-        float2 *x2 = (float2 *)x, *s2 = (float2 *)svol;
-        if (cbits && cflag && al8(cbits)) {
-            const uint2 *m2 = (const uint2 *)cbits;
-            if (B <= 8) hipLaunchKernelGGL((k_project_bits<MODE, 8>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, m2, cflag, Y2, S2, x2, s2);
-            else if (B <= 16) hipLaunchKernelGGL((k_project_bits<MODE, 16>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, m2, cflag, Y2, S2, x2, s2);
-            else if (B <= 24) hipLaunchKernelGGL((k_project_bits<MODE, 24>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, m2, cflag, Y2, S2, x2, s2);
-            else hipLaunchKernelGGL((k_project_bits<MODE, 32>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, m2, cflag, Y2, S2, x2, s2);
-            return;
-        }
-        if (B <= 8) hipLaunchKernelGGL((k_project_reg2<MODE, 8>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, Y2, S2, x2, s2);
-        else if (B <= 16) hipLaunchKernelGGL((k_project_reg2<MODE, 16>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, Y2, S2, x2, s2);
-        else if (B <= 24) hipLaunchKernelGGL((k_project_reg2<MODE, 24>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, Y2, S2, x2, s2);
-        else hipLaunchKernelGGL((k_project_reg2<MODE, 32>), g2, b, 0, s, npair, npix, B, ex, a1, a2, (const float2 *)w, t2, u2, C2, Y2, S2, x2, s2);
-        return;
-    }
-    if (B <= 8) hipLaunchKernelGGL((k_project_reg<MODE, 8>), g, b, 0, s, npix, B, ex, a1, a2, w, theta, u, C, Y, Sinv, x, svol);
-    else if (B <= 16) hipLaunchKernelGGL((k_project_reg<MODE, 16>), g, b, 0, s, npix, B, ex, a1, a2, w, theta, u, C, Y, Sinv, x, svol);
-    else if (B <= 32) hipLaunchKernelGGL((k_project_reg<MODE, 32>), g, b, 0, s, npix, B, ex, a1, a2, w, theta, u, C, Y, Sinv, x, svol);
-    else hipLaunchKernelGGL((k_project<MODE>), g, b, 0, s, npix, B, ex, a1, a2, w, theta, u, C, Y, Sinv, x, svol);
+    if (B <= 32 && cbits && cflag)
+        launch_project_reg<MODE>(ProjArgs{npix, B, ex, a1, a2, w, theta, u, C, cbits, cflag, Y, Sinv, x, svol, s});
+    else
+        hipLaunchKernelGGL((k_project<MODE>), dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, ex, a1, a2, w, theta,
+                           u, C, Y, Sinv, x, svol);
 }
 
 __global__ __launch_bounds__(kBlock) void k_copy4(uint32_t n4, const uint32_t *__restrict__ src,
