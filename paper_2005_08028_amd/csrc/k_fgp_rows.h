@@ -30,6 +30,21 @@
 // per-voxel arithmetic is that of the streaming and tiled kernels (same
 // helpers, same operand order, no contraction), so results are
 // bit-identical to theirs with float32 dual storage.
+//
+// What bounds it: vector instruction issue (17 per voxel-iteration for ITV2D,
+// v_rsq_f32 taking two slots), two wavefronts per SIMD. For a cold
+// 10-iteration ITV2D pass at 1024x1024x24 (128-row segments, 1,920
+// wavefronts), three things brought it there from 189 us:
+//   * The SIMD serves the older of its two wavefronts first. That one then
+//     runs as if alone (119 us) and the other is left to finish alone (185
+//     us), with the vector unit 70 % busy to the end. A priority that falls
+//     along each chunk of rows lets the one behind catch up: both end
+//     together, 187 -> 166 us (one change per chunk 171, none but a quarter
+//     of the segment 177).
+//   * Rows are read and written as bounded buffers (RowBuf): no masks, no
+//     vector addresses (748 -> 687 vector instructions per chunk).
+//   * The loads of a chunk are issued at its start and waited for at its end
+//     before the last stores, instead of behind them (200 -> 187 us).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -86,6 +101,7 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                                               RowRing<M, C> &rr)
 {
     using D = Dual<DT>;
+    using T = typename D::T;
     constexpr int CH = kRowChunk;
     constexpr int TW = 64 * C;
     constexpr int TXO = TW - 2 * M - 1; // interior columns per strip
@@ -98,19 +114,22 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     const int hi = min(a + H, nx);       // one past its last row
     const int j0 = sx * TXO - (M + 1) + lane * C;
 
-    bool jin[C], hj[C], outc[C];
+    // the strip's columns inside the image: jb .. jb + ncol, of which the first
+    // nhor carry a horizontal difference
+    const int jb = max(sx * TXO - (M + 1), 0);
+    const uint32_t ncol = (uint32_t)min(ny - jb, TW), nhor = (uint32_t)min(ny - 1 - jb, TW);
     float step_h[C];
-    uint32_t jcl[C];
+    uint32_t off_in[C], off_out[C]; // columns loaded and stored, from jb, in elements; kNoColumn: none
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int j = j0 + c;
-        jin[c] = j >= 0 && j < ny;
-        hj[c] = j >= 0 && j < ny - 1; // horizontal differences exist for 0 <= j < ny-1
-        step_h[c] = hj[c] ? step : 0.0f;
-        jcl[c] = jin[c] ? (uint32_t)j : 0u;
+        const bool hj = j >= 0 && j < ny - 1; // horizontal differences exist for 0 <= j < ny-1
+        step_h[c] = hj ? step : 0.0f;
+        off_in[c] = j >= jb && j < ny ? (uint32_t)(j - jb) : kNoColumn;
         const int cw = lane * C + c;
-        outc[c] = cw >= M + 1 && cw <= TW - 1 - M && j < ny;
+        off_out[c] = cw >= M + 1 && cw <= TW - 1 - M && j < ny ? (uint32_t)(j - jb) : kNoColumn;
     }
+    constexpr uint32_t SZ = (uint32_t)sizeof(T);
 #pragma unroll
     for (int s = 0; s < 2 * P; ++s)
 #pragma unroll
@@ -126,26 +145,36 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
 #pragma unroll
     for (int c = 0; c < C; ++c) cpm[c] = 0.0f;
 
-    // Chunk loads: x and (MODE >= 1) the starting duals of CH rows, from
-    // in-bounds addresses (row 0 / column 0 stand in for pixels outside the
-    // image), masked where consumed, so no load sits behind a branch.
+    // Chunk loads: x and (MODE >= 1) the starting duals of CH rows. Pixels
+    // outside the image and dual entries that carry no difference (column
+    // ny-1 of the horizontal channel, row nx-1 of the vertical one) lie
+    // outside their row's buffer and come back as 0.
     float xn[CH][C], lh[CH][C], lv[CH][C], mh[CH][C], mv[CH][C];
     auto load_chunk = [&](int i0) {
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
             const int i = i0 + s;
-            const uint32_t rowo = fo + ((i >= 0 && i < nx) ? (uint32_t)i : 0u) * (uint32_t)ny;
+            const bool iin = i >= 0 && i < nx;
+            const uint32_t rowo = fo + (iin ? (uint32_t)i : 0u) * (uint32_t)ny + (uint32_t)jb;
+            const uint32_t nh = iin ? nhor : 0u;                                // entries of p_h
+            const uint32_t nv = (uint32_t)i < (uint32_t)(nx - 1) ? ncol : 0u;   // and of p_v
+            const RowBuf xb = row_buf(x + rowo, iin ? ncol * 4u : 0u);
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const uint32_t o = rowo + jcl[c];
-                xn[s][c] = x[o];
-                if (MODE >= 1) {
-                    lh[s][c] = D::ld(pc, o);
-                    lv[s][c] = D::ld(pc, V + o);
+            for (int c = 0; c < C; ++c) xn[s][c] = row_ld<DT_F32>(xb, off_in[c] * 4u);
+            if (MODE >= 1) {
+                const RowBuf hb = row_buf(pc + rowo, nh * SZ), vb = row_buf(pc + (size_t)V + rowo, nv * SZ);
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    lh[s][c] = row_ld<DT>(hb, off_in[c] * SZ);
+                    lv[s][c] = row_ld<DT>(vb, off_in[c] * SZ);
                 }
-                if (MODE == 2) {
-                    mh[s][c] = D::ld(pp, o);
-                    mv[s][c] = D::ld(pp, V + o);
+            }
+            if (MODE == 2) {
+                const RowBuf hb = row_buf(pp + rowo, nh * SZ), vb = row_buf(pp + (size_t)V + rowo, nv * SZ);
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    mh[s][c] = row_ld<DT>(hb, off_in[c] * SZ);
+                    mv[s][c] = row_ld<DT>(vb, off_in[c] * SZ);
                 }
             }
         }
@@ -164,41 +193,52 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     const int nsteps = H + 2 * M + 1;
     const int nchunk = (nsteps + CH - 1) / CH; // >= M + 1 > NPRO
     constexpr int NPRO = (2 * (M - 1) + CH - 1) / CH;
+    // The rows loaded during a chunk go to the ring (and are waited for) at its
+    // end, before its last stores: a wait further on would wait for those
+    // stores too, which vmcnt counts with the loads.
+    auto settle_chunk = [&](int i0) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < CH; ++s) {
+            const int slot = (((i0 + s) % P) + P) % P;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (MODE >= 1) {
+                    settle(lh[s][c]);
+                    settle(lv[s][c]);
+                }
+                if (MODE == 2) {
+                    settle(mh[s][c]);
+                    settle(mv[s][c]);
+                }
+                ring[slot][lane * C + c] = xn[s][c];
+                ring[slot + P][lane * C + c] = xn[s][c];
+            }
+        }
+    };
     load_chunk(k_start + 1);
+    settle_chunk(k_start + 1);
     auto chunk = [&](int b, auto pro) {
         constexpr int PB = decltype(pro)::value; // prologue chunk index, or -1
         const int k0 = k_start + b * CH;
-        // level-0 inputs of the chunk's rows k0+1 .. k0+CH, masked
+        // level-0 inputs of the chunk's rows k0+1 .. k0+CH
         float i0h[CH][C], i0v[CH][C], j0h[CH][C], j0v[CH][C];
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
-            const int i = k0 + s + 1;
-            const bool iin = i >= 0 && i < nx;
-            const bool ivd = i >= 0 && i < nx - 1;
-            const int slot = ((i % P) + P) % P;
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const float v = (iin && jin[c]) ? xn[s][c] : 0.0f;
-                ring[slot][lane * C + c] = v;
-                ring[slot + P][lane * C + c] = v;
-                const bool hin = iin && hj[c];  // horizontal difference exists
-                const bool vin = ivd && jin[c]; // vertical difference exists
                 if (MODE == 0) {
                     i0h[s][c] = i0v[s][c] = j0h[s][c] = j0v[s][c] = 0.0f;
                 } else {
-                    j0h[s][c] = hin ? lh[s][c] : 0.0f;
-                    j0v[s][c] = vin ? lv[s][c] : 0.0f;
-                    if (MODE == 2) {
-                        i0h[s][c] = hin ? extrapolate(j0h[s][c], mh[s][c], bt.b[0]) : 0.0f;
-                        i0v[s][c] = vin ? extrapolate(j0v[s][c], mv[s][c], bt.b[0]) : 0.0f;
-                    } else {
-                        i0h[s][c] = j0h[s][c];
-                        i0v[s][c] = j0v[s][c];
-                    }
+                    j0h[s][c] = lh[s][c];
+                    j0v[s][c] = lv[s][c];
+                    i0h[s][c] = MODE == 2 ? extrapolate(lh[s][c], mh[s][c], bt.b[0]) : lh[s][c];
+                    i0v[s][c] = MODE == 2 ? extrapolate(lv[s][c], mv[s][c], bt.b[0]) : lv[s][c];
                 }
             }
         }
         load_chunk(k0 + CH + 1);
+        issued();
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
             const int k = k0 + s;
@@ -216,6 +256,17 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
 #pragma unroll
             for (int t = 0; t < M; ++t) {
                 if (PB >= 0 && PB * CH + s < 2 * t) break; // this level and the later ones are idle
+                // priority falls along a chunk, half a step at a time (see the
+                // header comment): the co-resident wavefront that is behind in
+                // its chunk goes first
+                if (t == 0) {
+                    if (s == 0) __builtin_amdgcn_s_setprio(3);
+                    else __builtin_amdgcn_s_setprio(1);
+                }
+                if (t == M / 2) {
+                    if (s == 0) __builtin_amdgcn_s_setprio(2);
+                    else __builtin_amdgcn_s_setprio(0);
+                }
                 const int r = k - t;
                 // theta_t of row r+1 = x - lambda D^T w_t
                 float thn[C];
@@ -224,7 +275,7 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                     const float whl = c > 0 ? ih[c - 1] : from_left(ih[C - 1]);
                     thn[c] = theta_of(ring[base - t][lane * C + c], whl, ih[c], cwv[t][c], iv[c], lam);
                 }
-                const float step_v = (r >= 0 && r < nx - 1) ? step : 0.0f; // uniform per row
+                const float step_v = row_step(r, nx, step);
                 const float bnext = bt.b[t + 1];
                 float oh[C], ov[C], nh[C], nv[C];
 #pragma unroll
@@ -280,7 +331,10 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                     jv[c] = nv[c];
                 }
             }
-            if (PB >= 0) continue; // the theta row is above the segment
+            if (PB >= 0) { // the theta row is above the segment
+                if (s == CH - 1) settle_chunk(k0 + CH + 1);
+                continue;
+            }
             // row r = k - M + 1 now has p^(s0+M) in jh, jv: theta = x - lambda D^T p
             const int r = k - M + 1;
             float th[C], xr[C];
@@ -291,23 +345,32 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                 th[c] = theta_of(xr[c], phl, jh[c], cpm[c], jv[c], lam);
                 cpm[c] = jv[c];
             }
+            if (s == CH - 1) settle_chunk(k0 + CH + 1);
             if (r >= a && r < hi) { // uniform
-                const uint32_t rowo = fo + (uint32_t)r * (uint32_t)ny;
+                const uint32_t rowo = fo + (uint32_t)r * (uint32_t)ny + (uint32_t)jb;
+                auto put = [&](float *out, const float(&v)[C]) {
+                    const RowBuf b = row_buf(out + rowo, ncol * 4u);
 #pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    if (!outc[c]) continue;
-                    const uint32_t o = rowo + (uint32_t)(j0 + c);
-                    if (theta_out) theta_out[o] = th[c];
-                    if (u_out) u_out[o] = xr[c] - th[c];
-                    if (pn_out) {
-                        D::st(pn_out, o, jh[c]);
-                        D::st(pn_out, V + o, jv[c]);
+                    for (int c = 0; c < C; ++c) row_st(b, off_out[c] * 4u, v[c]);
+                };
+                auto put_dual = [&](T *out, const float(&h)[C], const float(&v)[C]) {
+                    const RowBuf hb = row_buf(out + rowo, ncol * SZ);
+                    const RowBuf vb = row_buf(out + (size_t)V + rowo, ncol * SZ);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        row_st(hb, off_out[c] * SZ, D::to(h[c]));
+                        row_st(vb, off_out[c] * SZ, D::to(v[c]));
                     }
-                    if (MOM && pp_out) {
-                        D::st(pp_out, o, qph[c]);
-                        D::st(pp_out, V + o, qpv[c]);
-                    }
+                };
+                if (theta_out) put(theta_out, th);
+                if (u_out) {
+                    float uu[C];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) uu[c] = xr[c] - th[c];
+                    put(u_out, uu);
                 }
+                if (pn_out) put_dual(pn_out, jh, jv);
+                if (MOM && pp_out) put_dual(pp_out, qph, qpv);
             }
         }
     };

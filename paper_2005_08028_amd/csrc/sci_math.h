@@ -24,6 +24,7 @@ template <> struct Dual<DT_F32> {
     using T = float;
     __device__ static inline float cvt(T v) { return v; }
     __device__ static inline float ld(const T *p, uint32_t i) { return p[i]; }
+    __device__ static inline T to(float v) { return v; }
     __device__ static inline void st(T *p, uint32_t i, float v) { p[i] = v; }
 };
 
@@ -32,13 +33,14 @@ template <> struct Dual<DT_BF16> {
     using T = uint16_t;
     __device__ static inline float cvt(T v) { return __uint_as_float((uint32_t)v << 16); }
     __device__ static inline float ld(const T *p, uint32_t i) { return cvt(p[i]); }
-    __device__ static inline void st(T *p, uint32_t i, float v)
+    __device__ static inline T to(float v)
     {
         uint32_t u = __float_as_uint(v);
         uint32_t r = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
         if ((u & 0x7fffffffu) > 0x7f800000u) r = (u >> 16) | 0x40u; // keep NaN a NaN
-        p[i] = (uint16_t)r;
+        return (uint16_t)r;
     }
+    __device__ static inline void st(T *p, uint32_t i, float v) { p[i] = to(v); }
 };
 
 // IEEE binary16: hardware conversion (round to nearest even).
@@ -46,7 +48,8 @@ template <> struct Dual<DT_F16> {
     using T = _Float16;
     __device__ static inline float cvt(T v) { return (float)v; }
     __device__ static inline float ld(const T *p, uint32_t i) { return cvt(p[i]); }
-    __device__ static inline void st(T *p, uint32_t i, float v) { p[i] = (_Float16)v; }
+    __device__ static inline T to(float v) { return (_Float16)v; }
+    __device__ static inline void st(T *p, uint32_t i, float v) { p[i] = to(v); }
 };
 
 // ---- the FGP step ---------------------------------------------------------
@@ -72,11 +75,16 @@ __device__ inline float ascend(float w, float z, float step) { return fmaf(step,
 __device__ inline float from_left(float v) { return __builtin_amdgcn_update_dpp(0.0f, v, 0x138, 0xF, 0xF, true); }
 __device__ inline float from_right(float v) { return __builtin_amdgcn_update_dpp(0.0f, v, 0x130, 0xF, 0xF, true); }
 
-// ATV projection q / max(1, |q|): equal to clamping q to [-1, 1].
-__device__ inline float proj_atv(float q) { return fminf(fmaxf(q, -1.0f), 1.0f); }
+// ATV projection q / max(1, |q|): equal to clamping q to [-1, 1]. One v_med3_f32
+// (a NaN gives -1, as the pair fmaxf, fminf does, which also costs a
+// canonicalising v_max_f32).
+__device__ inline float proj_atv(float q) { return __builtin_amdgcn_fmed3f(q, -1.0f, 1.0f); }
 
-// Isotropic scale 1 / max(1, sqrt(n2)) = min(1, 1/sqrt(n2)) for a squared norm n2.
-__device__ inline float iso_scale(float n2) { return fminf(1.0f, __builtin_amdgcn_rsqf(n2)); }
+// Isotropic scale 1 / max(1, sqrt(n2)) = min(1, 1/sqrt(n2)) for a squared norm
+// n2 >= 0. The median with 0 and 1 becomes the output clamp of v_rsq_f32 and
+// costs no instruction (fminf is one of the 18 of an ITV2D voxel-iteration).
+// A NaN norm gives 0.
+__device__ inline float iso_scale(float n2) { return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rsqf(n2), 0.0f, 1.0f); }
 
 // Semi-implicit (Chambolle 2004) scale 1 / (1 + sqrt(n2)) for the squared
 // norm n2 of z/(8 lambda), with the hardware square root and reciprocal
@@ -92,6 +100,58 @@ __device__ inline float semi_implicit_atv(float q, float s) { return q * __built
 
 // Squared-norm accumulation (h^2 + v^2 added to acc).
 __device__ inline float norm2_add(float acc, float h, float v) { return fmaf(v, v, fmaf(h, h, acc)); }
+
+// The step of a row's vertical differences: step where 0 <= r < nx - 1, else 0,
+// for a row r that is uniform over the wavefront. Selected as an integer, which
+// the scalar unit does (a float select takes a vector instruction).
+__device__ inline float row_step(int r, int nx, float step)
+{
+    return __int_as_float(__float_as_int(step) & -(int)((uint32_t)r < (uint32_t)(nx - 1)));
+}
+
+// ---- image rows as bounded buffers ------------------------------------------
+//
+// The columns of an image row that a strip of lanes covers, as a raw buffer
+// resource: the address is wavefront-uniform (scalar), a lane gives its byte
+// offset in 32 bits, and the hardware's range check stands in for the masks of
+// a stencil's edges: a load at an offset >= `bytes` returns 0 and a store there
+// is dropped. bytes = 0 makes a row that does not exist. This spares the
+// 64-bit vector address of every access, the selects on the loaded values and
+// the execution masks around the stores.
+using RowBuf = __amdgpu_buffer_rsrc_t;
+constexpr uint32_t kNoColumn = 1u << 27; // element offset of a lane that takes no part: past any strip
+
+template <typename T> __device__ inline RowBuf row_buf(const T *row, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)const_cast<T *>(row), 0, (int)bytes, 0x00020000);
+}
+template <int DT> __device__ inline float row_ld(RowBuf b, uint32_t off)
+{
+    using T = typename Dual<DT>::T;
+    if constexpr (DT == DT_F32)
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+    else
+        return Dual<DT>::cvt(__builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(b, (int)off, 0, 0)));
+}
+__device__ inline void row_st(RowBuf b, uint32_t off, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)off, 0, 0);
+}
+__device__ inline void row_st(RowBuf b, uint32_t off, uint16_t v)
+{
+    __builtin_amdgcn_raw_buffer_store_b16(v, b, (int)off, 0, 0);
+}
+__device__ inline void row_st(RowBuf b, uint32_t off, _Float16 v)
+{
+    row_st(b, off, __builtin_bit_cast(uint16_t, v));
+}
+
+// Keep a prefetch where it stands: memory reads above cannot sink below (the
+// compiler otherwise moves loads whose values only the next loop iteration
+// uses to the loop's end, where their latency is exposed).
+__device__ __forceinline__ void issued() { asm volatile("" ::: "memory"); }
+// Wait here for the load that fills v.
+__device__ __forceinline__ void settle(float &v) { asm volatile("" : "+v"(v)); }
 
 // ---- work mapping -----------------------------------------------------------
 
