@@ -22,6 +22,15 @@
 // registers (an LDS ring per frame would not fit next to B frames of state).
 // Levels the pipeline fill has not reached are left out of the first chunks
 // at compile time, as in the 2D kernel.
+//
+// What bounds it: the latency of the exchanges; a wavefront waits 37 % of its
+// time and the vector unit is 55 % to 70 % busy. Raising the priority of a
+// wavefront that is on its way to an exchange's barrier took passes of 5 from
+// 30.9 to 27.8 us at 512x512x10 and from 151 + 222 to 148 + 216 us at
+// 1024x1024x24 (cold, and from the records); two barriers per round, one for
+// each step, with the reads of one step's partials under the work of the other
+// did not help (31.3, 182 + 224 us), nor did bounded row buffers as in the 2D
+// kernel (their scalar instructions sit on the critical path: 176 + 217 us).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -79,8 +88,8 @@ template <int DT> __device__ inline uint32_t vtv_pack16(float a, float b)
     else return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, vtv_h2));
 }
 
-template <int M, int KF, int MODE, int CH_STEP, int DT = DT_F32, int QIO = 0>
-__global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, int B, int fpw, int nstrip, int H,
+template <int M, int KF, int MODE, int CH_STEP, int DT, int QIO, int NS>
+__global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int fpw, int nstrip, int H,
                                                               const float *__restrict__ x,
                                                               const typename Dual<DT>::T *__restrict__ pc,
                                                               const typename Dual<DT>::T *__restrict__ pp,
@@ -97,7 +106,7 @@ __global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, 
     constexpr int TXO = 64 - 2 * M - 1; // interior columns per strip
     static_assert(TXO > 0, "strip too narrow for the pass length");
     static_assert(CH == 2, "steps run in pairs, one pair per chunk");
-    __shared__ float2 n2s[2][kVtvMaxWaves][64]; // (step k, step k+1) partials
+    __shared__ float2 n2s[2][NS][64]; // (step k, step k+1) partials
 
     const int ng = (int)(blockDim.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -142,8 +151,8 @@ __global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, 
     // no loop over ng); the slots of absent wavefronts hold +0, which leaves
     // the non-negative sum unchanged. The first exchange's barrier orders
     // these writes before any read.
-    for (int e = (int)threadIdx.x; e < 2 * kVtvMaxWaves * 64; e += (int)blockDim.x)
-        if ((e >> 6) % kVtvMaxWaves >= ng) (&n2s[0][0][0])[e] = make_float2(0.0f, 0.0f);
+    for (int e = (int)threadIdx.x; e < 2 * NS * 64; e += (int)blockDim.x)
+        if ((e >> 6) % NS >= ng) (&n2s[0][0][0])[e] = make_float2(0.0f, 0.0f);
 
     // Chunk loads of CH rows for every frame slot, from in-bounds addresses,
     // masked where consumed.
@@ -197,11 +206,14 @@ __global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, 
         for (int s = 0; s < CH; ++s) {
             const int i = k0 + s + 1;
             const bool iin = i >= 0 && i < nx;
-            const bool hin = iin && hj;                      // horizontal difference exists
-            const bool vin = i >= 0 && i < nx - 1 && jin;    // vertical difference exists
 #pragma unroll
             for (int kk = 0; kk < KF; ++kk) {
-                x0[s][kk] = (iin && jin) ? xn[s][kk] : 0.0f;
+                // a slot past the last frame holds x = p = 0 and adds nothing
+                // to the norm
+                const bool real = kk < nk;
+                const bool hin = iin && hj && real;                   // horizontal difference exists
+                const bool vin = i >= 0 && i < nx - 1 && jin && real; // vertical difference exists
+                x0[s][kk] = (iin && jin && real) ? xn[s][kk] : 0.0f;
                 if (MODE == 0) {
                     i0h[s][kk] = i0v[s][kk] = j0h[s][kk] = j0v[s][kk] = 0.0f;
                 } else {
@@ -254,25 +266,23 @@ __global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, 
             float thn[2][KF], qh[2][KF], qv[2][KF], n2[2] = {0.0f, 0.0f};
             auto pre = [&](int sidx, int t) {
                 const int r = k0 + sidx - t;
-                const float step_v = (r >= 0 && r < nx - 1) ? step : 0.0f; // uniform per row
+                const float step_v = row_step(r, nx, step);
 #pragma unroll
                 for (int kk = 0; kk < KF; ++kk) {
                     thn[sidx][kk] = theta_of(xl[t + 1 - sidx][kk], from_left(ih[sidx][kk]), ih[sidx][kk], cwv[t][kk],
                                              iv[sidx][kk], lam);
                     const float zh = from_right(cth[t][kk]) - cth[t][kk];
                     const float zv = thn[sidx][kk] - cth[t][kk];
-                    float n2a;
                     if (CH_STEP) {
                         const float sh = step_h * zh, sv = step_v * zv;
                         qh[sidx][kk] = cwh[t][kk] + sh;
                         qv[sidx][kk] = cwv[t][kk] + sv;
-                        n2a = norm2_add(n2[sidx], sh, sv);
+                        n2[sidx] = norm2_add(n2[sidx], sh, sv);
                     } else {
                         qh[sidx][kk] = ascend(cwh[t][kk], zh, step_h);
                         qv[sidx][kk] = ascend(cwv[t][kk], zv, step_v);
-                        n2a = norm2_add(n2[sidx], qh[sidx][kk], qv[sidx][kk]);
+                        n2[sidx] = norm2_add(n2[sidx], qh[sidx][kk], qv[sidx][kk]);
                     }
-                    n2[sidx] = kk < nk ? n2a : n2[sidx];
                 }
             };
             auto post = [&](int sidx, int t, float tot) {
@@ -298,13 +308,17 @@ __global__ __launch_bounds__(64 * kVtvMaxWaves) void k_vtv_rows(int nx, int ny, 
                     jv[sidx][kk] = nv;
                 }
             };
+            // a wavefront on its way to the barrier goes before one that has
+            // passed it: the barrier waits for the last
+            __builtin_amdgcn_s_setprio(2);
             if (runA) pre(0, tau);
             if (runB) pre(1, tau - 1);
             n2s[par][g][lane] = make_float2(n2[0], n2[1]);
             lds_barrier();
+            __builtin_amdgcn_s_setprio(0);
             float totA = 0.0f, totB = 0.0f;
 #pragma unroll
-            for (int gg = 0; gg < kVtvMaxWaves; ++gg) {
+            for (int gg = 0; gg < NS; ++gg) {
                 const float2 v2 = n2s[par][gg][lane];
                 totA += v2.x;
                 totB += v2.y;
@@ -407,18 +421,34 @@ int vtv_segment_rows(K kernel, int ng, int nx, int nstrip)
     return (nx + nseg - 1) / nseg;
 }
 
-template <int M, int KF, int MODE, int CH_STEP, int DT, int QIO = 0>
-void launch_vtv_mode(int nx, int ny, int B, int fpw, int ng, const float *x, const TilePass &tp, float lam,
-                     hipStream_t s)
+// NS: slots of the norm exchange and most wavefronts of a workgroup. Five serve
+// the 5 wavefronts of B = 9 and 10 (two frames each; float32 projection step): the
+// three absent slots are 36 of the ~440 vector instructions of a 2-row chunk.
+template <int M, int KF, int MODE, int CH_STEP, int DT, int QIO, int NS>
+void launch_vtv_slots(int nx, int ny, int B, int fpw, int ng, const float *x, const TilePass &tp, float lam,
+                      hipStream_t s)
 {
     using T = typename Dual<DT>::T;
     constexpr int TXO = 64 - 2 * M - 1;
     const int nstrip = (ny + TXO - 1) / TXO;
-    const int H = vtv_segment_rows(k_vtv_rows<M, KF, MODE, CH_STEP, DT, QIO>, ng, nx, nstrip);
+    const int H = vtv_segment_rows(k_vtv_rows<M, KF, MODE, CH_STEP, DT, QIO, NS>, ng, nx, nstrip);
     const int nseg = (nx + H - 1) / H;
-    hipLaunchKernelGGL((k_vtv_rows<M, KF, MODE, CH_STEP, DT, QIO>), dim3(nstrip * nseg), dim3(64 * ng), 0, s, nx, ny,
-                       B, fpw, nstrip, H, x, (const T *)tp.pc, (const T *)tp.pp, tp.beta, lam, 1.0f / (8.0f * lam),
+    hipLaunchKernelGGL((k_vtv_rows<M, KF, MODE, CH_STEP, DT, QIO, NS>), dim3(nstrip * nseg), dim3(64 * ng), 0, s, nx,
+                       ny, B, fpw, nstrip, H, x, (const T *)tp.pc, (const T *)tp.pp, tp.beta, lam, 1.0f / (8.0f * lam),
                        (T *)tp.pn_out, (T *)tp.pp_out, tp.theta, tp.u_out);
+}
+
+template <int M, int KF, int MODE, int CH_STEP, int DT, int QIO = 0>
+void launch_vtv_mode(int nx, int ny, int B, int fpw, int ng, const float *x, const TilePass &tp, float lam,
+                     hipStream_t s)
+{
+    if constexpr (KF == 2 && !CH_STEP && DT == DT_F32) { // more frames per wavefront always take 6 or more
+        if (ng <= 5) {
+            launch_vtv_slots<M, KF, MODE, CH_STEP, DT, QIO, 5>(nx, ny, B, fpw, ng, x, tp, lam, s);
+            return;
+        }
+    }
+    launch_vtv_slots<M, KF, MODE, CH_STEP, DT, QIO, kVtvMaxWaves>(nx, ny, B, fpw, ng, x, tp, lam, s);
 }
 
 // Pass lengths with dual-record variants: projection passes of at least 3
