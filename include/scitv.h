@@ -109,13 +109,15 @@ typedef struct {
     int32_t n_inner_max;
     int32_t gap_check_every;
     int32_t tile_shape;      /* fused schedule: 0 = autotuned for this problem (sci_autotune) or the
-                                default (a cold call of at most 10 iterations whose dual is not
-                                returned: the row-pipelined shape that best fills the GPU when
-                                the problem is large enough; otherwise shape 1); k >= 1 = shape k
+                                default (the shape and pass count with the smallest estimated time
+                                for the problem's size, the iterations and the duals that the call
+                                reads and returns; with float32 duals every choice gives the same
+                                bits; passes that touch 16-bit duals run shape 1); k >= 1 = shape k
                                 (see sci_tile_shape_info) */
     int32_t tile_passes;     /* fused schedule: passes over HBM per denoiser call (each runs about
                                 n_inner / tile_passes iterations, at most 10); 0 = autotuned or
-                                default (passes of about 5 iterations; VTV: the fewest passes its
+                                default (chosen with the shape; passes of about 5 iterations where
+                                16-bit duals are rounded between them; VTV: the fewest passes its
                                 kernel runs) */
     int32_t chambolle04;     /* 1 = Chambolle's (2004) semi-implicit step (Sec. 2.3):
                                 p = (w + z/(8 lambda)) / (1 + |z|/(8 lambda)), z = D theta, |z| per
@@ -273,7 +275,7 @@ typedef struct {
  * ignored (the dual never leaves the chip); otherwise SCI_ERR_UNSUPPORTED.
  * Outputs of different problems must not overlap. The tile shape (ATV,
  * ITV2D) is p->tv.tile_shape, else the one sci_autotune_batched chose for
- * this batch, else the default. */
+ * this batch, else chosen by the sizes of the problems still iterating. */
 int sci_gap_tv_batched(sci_ctx *ctx, int32_t n, const sci_problem *probs, const sci_solver_params *p,
                        hipStream_t stream);
 
@@ -369,7 +371,8 @@ int sci_gap_tv_adaptive(sci_ctx *ctx, sci_dims d, const sci_solver_params *p, co
 
 /* ---- tile-shape autotuning of the fused schedule -------------------------- */
 
-/* Number of shapes of the fused denoiser (tiled, then row-pipelined). */
+/* Number of shapes of the fused denoiser (tiled and row-pipelined, see
+ * sci_tile_shape_pipelined). */
 int sci_tile_shape_count(void);
 
 /* Shape k (1-based, as in sci_tv_params.tile_shape). Tiled shape: a

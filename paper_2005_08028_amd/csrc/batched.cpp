@@ -19,13 +19,20 @@ namespace {
 
 constexpr int kPixBlock = 256;
 
+// The problems sorted by descending outer_iters, so that those still active are
+// a prefix, as one or two device tables that differ in the denoise launch's
+// shape (ATV, ITV2D): an uneven batch ends with few problems, which fill the
+// chip with other shapes than all of them.
 struct BatchPlan {
-    std::vector<BatchProb> tab; // sorted by descending outer_iters
-    std::vector<int> order;     // tab[k] is problem order[k]
-    std::vector<int> wg_end;    // wg_end[k] = workgroups of problems 0..k-1 (prefix)
+    int n = 0, ntab = 1;
+    std::vector<BatchProb> tab; // ntab tables of n problems
+    std::vector<int> order;     // problem k of a table is problem order[k] of the caller
+    std::vector<int> wg_end[2]; // per table: workgroups of problems 0..k-1 (prefix)
     std::vector<int> pb_end;
     std::vector<int> pj_end;
-    int maxB = 0, Tmax = 0, shape = 0, m = 0;
+    std::vector<char> use;      // use[k]: table of a denoise launch over the first k problems
+    int maxB = 0, Tmax = 0, m = 0;
+    int shape[2] = {0, 0};
     size_t slab_floats = 0;
 };
 
@@ -76,23 +83,69 @@ int validate(sci_ctx *ctx, int n, const sci_problem *probs, const sci_solver_par
     return SCI_OK;
 }
 
+// Untuned shapes: the pair, and for every number of active problems the one of
+// the two, with the smallest estimated sum of the solve's denoise launches
+// (each choice gives the same bits). 12 measurements of 256^2 to 1024^2, 5 ATV
+// iterations: 102 us per launch over all of them and 15 us over the last with
+// shape 1 (the earlier default), 68 and 15 us with the pair; one
+// row-pipelined shape for both 68 and 38 us.
+void choose_shapes(const sci_ctx *ctx, const sci_problem *probs, const sci_solver_params &p, const std::vector<int> &T,
+                   BatchPlan &pl)
+{
+    const int n = pl.n, ns = tile_shape_count();
+    std::vector<double> cost((size_t)ns * (n + 1), 0.0); // of one launch over the first k problems
+    for (int sh = 0; sh < ns; ++sh) {
+        long units = 0;
+        double voxels = 0.0;
+        for (int k = 0; k < n; ++k) {
+            const sci_dims &d = probs[pl.order[k]].d;
+            units += tile_units(sh, pl.m, d.nx, d.ny) * d.B;
+            voxels += (double)d.nx * d.ny * d.B;
+            cost[(size_t)sh * (n + 1) + k + 1] = tile_pass_us(ctx->num_cus, p.tv.tv, sh, pl.m, units, voxels, 2);
+        }
+    }
+    auto launches = [&](int k) { return (double)(T[k - 1] - (k < n ? T[k] : 0)); }; // over the first k problems
+    double best = -1.0;
+    for (int a = 0; a < ns; ++a)
+        for (int b = a; b < ns; ++b) {
+            double t = 0.0;
+            for (int k = 1; k <= n; ++k)
+                t += launches(k) * std::min(cost[(size_t)a * (n + 1) + k], cost[(size_t)b * (n + 1) + k]);
+            if (best < 0.0 || t < best) {
+                best = t;
+                pl.shape[0] = a;
+                pl.shape[1] = b;
+            }
+        }
+    pl.ntab = pl.shape[0] == pl.shape[1] ? 1 : 2;
+    for (int k = 1; k <= n; ++k)
+        pl.use[k] = pl.ntab == 2 &&
+                    cost[(size_t)pl.shape[1] * (n + 1) + k] < cost[(size_t)pl.shape[0] * (n + 1) + k];
+}
+
 void plan_batch(const sci_ctx *ctx, int n, const sci_problem *probs, const sci_solver_params &p, int shape_override,
                 BatchPlan &pl)
 {
     pl.m = p.tv.n_inner;
-    pl.shape = 0;
-    auto it = ctx->tuned.find(batch_key(p, n, probs));
-    if (it != ctx->tuned.end()) pl.shape = it->second.first;
-    if (p.tv.tile_shape >= 1) pl.shape = p.tv.tile_shape - 1;
-    if (shape_override >= 0) pl.shape = shape_override;
-    int tw = 0, th = 0;
-    batch_tile_extent(pl.shape, pl.m, &tw, &th);
+    pl.n = n;
     pl.order.resize(n);
     std::iota(pl.order.begin(), pl.order.end(), 0);
     auto T = [&](int i) { return probs[i].outer_iters > 0 ? probs[i].outer_iters : p.outer_iters; };
     std::stable_sort(pl.order.begin(), pl.order.end(), [&](int a, int b) { return T(a) > T(b); });
-    pl.tab.assign(n, BatchProb{});
-    pl.wg_end.assign(n + 1, 0);
+    pl.ntab = 1;
+    pl.shape[0] = pl.shape[1] = 0;
+    pl.use.assign(n + 1, 0);
+    auto it = ctx->tuned.find(batch_key(p, n, probs));
+    if (shape_override >= 0) pl.shape[0] = shape_override;
+    else if (p.tv.tile_shape >= 1) pl.shape[0] = p.tv.tile_shape - 1;
+    else if (it != ctx->tuned.end()) pl.shape[0] = it->second.first;
+    else if (tile_supported(p.tv.tv)) {
+        std::vector<int> iters(n);
+        for (int k = 0; k < n; ++k) iters[k] = T(pl.order[k]);
+        choose_shapes(ctx, probs, p, iters, pl);
+    }
+    pl.tab.assign((size_t)pl.ntab * n, BatchProb{});
+    for (int v = 0; v < pl.ntab; ++v) pl.wg_end[v].assign(n + 1, 0);
     pl.pb_end.assign(n + 1, 0);
     pl.pj_end.assign(n + 1, 0);
     pl.slab_floats = 0;
@@ -100,16 +153,12 @@ void plan_batch(const sci_ctx *ctx, int n, const sci_problem *probs, const sci_s
     pl.Tmax = 0;
     for (int k = 0; k < n; ++k) {
         const sci_problem &q = probs[pl.order[k]];
-        BatchProb &b = pl.tab[k];
+        BatchProb b{};
         b.nx = q.d.nx;
         b.ny = q.d.ny;
         b.B = q.d.B;
         b.outer_iters = T(pl.order[k]);
-        b.ntx = (q.d.ny + tw - 1) / tw;
-        b.ntiles = b.ntx * ((q.d.nx + th - 1) / th);
-        b.wg_base = pl.wg_end[k];
         b.pb_base = pl.pb_end[k];
-        pl.wg_end[k + 1] = b.wg_base + b.ntiles * b.B;
         const int npix = q.d.nx * q.d.ny;
         pl.pb_end[k + 1] = b.pb_base + (npix + kPixBlock - 1) / kPixBlock;
         auto al8 = [](const void *ptr) { return ptr == nullptr || ((uintptr_t)ptr & 7u) == 0; };
@@ -121,6 +170,15 @@ void plan_batch(const sci_ctx *ctx, int n, const sci_problem *probs, const sci_s
         b.C = q.C;
         b.x = q.X_out;
         b.theta = q.Theta_out;
+        for (int v = 0; v < pl.ntab; ++v) {
+            int tw = 0, th = 0;
+            batch_tile_extent(pl.shape[v], pl.m, &tw, &th);
+            b.ntx = (q.d.ny + tw - 1) / tw;
+            b.ntiles = b.ntx * ((q.d.nx + th - 1) / th);
+            b.wg_base = pl.wg_end[v][k];
+            pl.wg_end[v][k + 1] = b.wg_base + b.ntiles * b.B;
+            pl.tab[(size_t)v * n + k] = b;
+        }
         pl.slab_floats += 2 * (((size_t)npix + 63) & ~(size_t)63) + 64; // Sinv, mask bits, flag
         if (!q.Theta_out) pl.slab_floats += ((size_t)npix * q.d.B + 63) & ~(size_t)63;
         pl.maxB = std::max(pl.maxB, b.B);
@@ -131,7 +189,8 @@ void plan_batch(const sci_ctx *ctx, int n, const sci_problem *probs, const sci_s
 void bind_slab(float *slab, BatchPlan &pl)
 {
     size_t off = 0;
-    for (BatchProb &b : pl.tab) {
+    for (int k = 0; k < pl.n; ++k) {
+        BatchProb &b = pl.tab[k];
         const size_t npix = (size_t)b.nx * b.ny;
         b.Sinv = slab + off;
         off += (npix + 63) & ~(size_t)63;
@@ -143,20 +202,27 @@ void bind_slab(float *slab, BatchPlan &pl)
             b.theta = slab + off;
             off += (npix * b.B + 63) & ~(size_t)63;
         }
+        for (int v = 1; v < pl.ntab; ++v) {
+            BatchProb &c = pl.tab[(size_t)v * pl.n + k];
+            c.Sinv = b.Sinv;
+            c.cbits = b.cbits;
+            c.cflag = b.cflag;
+            c.theta = b.theta;
+        }
     }
 }
 
 int active_count(const BatchPlan &pl, int t)
 {
     int k = 0;
-    while (k < (int)pl.tab.size() && pl.tab[k].outer_iters > t) ++k;
+    while (k < pl.n && pl.tab[k].outer_iters > t) ++k;
     return k;
 }
 
 int enqueue_batch(sci_ctx *ctx, const BatchPlan &pl, const BatchProb *tab_dev, const sci_solver_params &p,
                   hipStream_t s)
 {
-    const int n = (int)pl.tab.size();
+    const int n = pl.n;
     {
         ProfScope prof(ctx, PF_SETUP, s);
         launch_batch_setup(n, pl.pb_end[n], tab_dev, s);
@@ -190,7 +256,9 @@ int enqueue_batch(sci_ctx *ctx, const BatchPlan &pl, const BatchProb *tab_dev, c
             }
         } else {
             ProfScope prof(ctx, PF_FGP_FUSED, s);
-            st = launch_batch_denoise(p.tv.tv, pl.shape, pl.m, na, pl.wg_end[na], tab_dev, bt, p.tv.lambda, s);
+            const int v = pl.use[na];
+            st = launch_batch_denoise(p.tv.tv, pl.shape[v], pl.m, na, pl.wg_end[v][na], tab_dev + (size_t)v * n, bt,
+                                      p.tv.lambda, s);
         }
         if (st != SCI_OK) return fail(ctx, st, "batched denoise");
         if ((st = check_launch(ctx, "k_batch_denoise")) != SCI_OK) return st;
@@ -237,11 +305,12 @@ int sci_gap_tv_batched(sci_ctx *ctx, int32_t n, const sci_problem *probs, const 
         return enqueue_batch(ctx, pl, tab, *p, stream);
     }
     // graph: keyed by every pointer and size of the batch; owns its own table
-    std::string key = "batched|" + batch_key(*p, n, probs) + "|" + std::to_string(pl.shape) + "|" +
+    std::string key = "batched|" + batch_key(*p, n, probs) + "|" + std::to_string(pl.shape[0]) + "|" + std::to_string(pl.shape[1]) + "|" +
                       std::to_string(p->outer_iters) + "|" + std::to_string(p->tv.lambda) + "|" +
                       std::to_string(p->tv.accel);
     char buf[64];
-    for (const BatchProb &b : pl.tab) {
+    for (int k = 0; k < pl.n; ++k) {
+        const BatchProb &b = pl.tab[k];
         snprintf(buf, sizeof buf, "|%p,%p,%p,%p,%d", (const void *)b.Y, (const void *)b.C, (void *)b.x,
                  (void *)b.theta, b.outer_iters);
         key += buf;
@@ -320,14 +389,14 @@ int sci_autotune_batched(sci_ctx *ctx, int32_t n, const sci_problem *probs, cons
         bind_slab(slab, pl);
         // time the denoise of all problems on their first projection (outer_iters ignored)
         for (BatchProb &b : pl.tab) b.outer_iters = 1;
-        const int nb = (int)pl.tab.size();
+        const int nb = pl.n;
         if ((st = upload_table(ctx, pl, tab, stream)) != SCI_OK) break;
         launch_batch_setup(nb, pl.pb_end[nb], tab, stream);
         if ((st = launch_batch_project(nb, pl.pj_end[nb], pl.maxB, tab, stream)) != SCI_OK) break;
         const int reps = 3;
         for (int r = 0; r <= reps && st == SCI_OK; ++r) {
             if (r == 1 && hipEventRecord(e0, stream) != hipSuccess) st = fail(ctx, SCI_ERR_HIP, "hipEventRecord");
-            if (st == SCI_OK) st = launch_batch_denoise(p->tv.tv, sh, pl.m, nb, pl.wg_end[nb], tab, bt, p->tv.lambda, stream);
+            if (st == SCI_OK) st = launch_batch_denoise(p->tv.tv, sh, pl.m, nb, pl.wg_end[0][nb], tab, bt, p->tv.lambda, stream);
         }
         if (st != SCI_OK) break;
         if ((st = check_launch(ctx, "autotune batched")) != SCI_OK) break;

@@ -19,7 +19,7 @@ int launch_rows_ch_f32(int tv, int H, int m, int nx, int ny, int B, const float 
 
 bool tile_supported(int tv) { return tv == TV_ATV || tv == TV_ITV2D; }
 
-int tile_shape_count() { return kTileShapes + kRowShapes; }
+int tile_shape_count() { return kShapes; }
 
 bool tile_shape_info(int shape, int *rows, int *waves, int *cols)
 {
@@ -36,7 +36,7 @@ bool tile_shape_info(int shape, int *rows, int *waves, int *cols)
     return false;
 }
 
-bool tile_shape_pipelined(int shape) { return shape >= kTileShapes && shape < kTileShapes + kRowShapes; }
+bool tile_shape_pipelined(int shape) { return shape >= kFirstRowShape && shape < kFirstRowShape + kRowShapes; }
 
 int launch_fgp_tile(int tv, int dual_dtype, int m, int shape, int nx, int ny, int B, const float *x,
                     const TilePass &tp, float lam, hipStream_t s, bool chambolle04)

@@ -198,8 +198,11 @@ struct TilePass {
 bool tile_supported(int tv);
 int tile_shape_count();
 bool tile_shape_info(int shape, int *rows, int *waves, int *cols);
-// true for the row-pipelined shapes (numbered after the tiled ones)
+// true for the row-pipelined shapes
 bool tile_shape_pipelined(int shape);
+// Cost model of the fused 2D passes (tile_model.cpp).
+long tile_units(int shape, int m, int nx, int ny);
+double tile_pass_us(int num_cus, int tv, int shape, int m, long units, double voxels, int io);
 // Row-pipelined VTV passes: the longest pass for B frames (0 when the kernel
 // does not run them), and one pass of m iterations with the duals read and
 // written between passes in dual_dtype (16-bit: projection step only).

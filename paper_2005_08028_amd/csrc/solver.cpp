@@ -104,6 +104,7 @@ struct FgpRun {
     void *buf[4] = {nullptr, nullptr, nullptr, nullptr};
     void *quad[2] = {nullptr, nullptr}; // VTV: dual records between the passes of one call (when bound)
     size_t quad_bytes = 0;              // size of each record buffer
+    void *last_out = nullptr;   // where the last pass of a fixed-count call stores the dual (nullptr: a scratch buffer)
     const void *cur = nullptr;  // p^(s) (nullptr = zero)
     const void *prev = nullptr; // p^(s-1)
     int iters = 0;
@@ -132,7 +133,7 @@ constexpr const char *kFusedScope =
 
 int fgp_tile_iterate(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const float *x, FgpRun &r, int n,
                      float *theta, float *u_out, bool keep_dual, hipStream_t s, int force_shape = -1,
-                     int force_passes = -1);
+                     int force_passes = -1, bool more = false);
 int stream_tile_shape(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d);
 
 // Enqueue `n` more inner iterations of the streaming schedule: one pass over
@@ -142,10 +143,10 @@ int fgp_iterate(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const f
                 hipStream_t s)
 {
     if (tile_supported(p.tv) && !p.chambolle04)
-        return fgp_tile_iterate(ctx, d, p, x, r, n, nullptr, nullptr, true, s, stream_tile_shape(ctx, p, d), n);
+        return fgp_tile_iterate(ctx, d, p, x, r, n, nullptr, nullptr, true, s, stream_tile_shape(ctx, p, d), n, true);
     for (int it = 0; it < n; ++it) {
         const int mode = r.mode(p);
-        void *out = r.free_buffer();
+        void *out = it == n - 1 && r.last_out ? r.last_out : r.free_buffer();
         ProfScope prof(ctx, PF_FGP_STREAM, s);
         auto launch = p.chambolle04 ? launch_fgp_stream_chambolle04 : launch_fgp_stream;
         int st = launch(p.tv, p.dual_dtype, d.nx, d.ny, d.B, x, r.cur, r.prev ? r.prev : r.cur, out, mode,
@@ -210,23 +211,68 @@ int default_row_shape(const sci_ctx *ctx, const sci_dims &d, int m)
     return best >= 0 && 2 * best_waves >= slots ? best : -1;
 }
 
-// Tile shape and number of passes of the fused schedule: explicit
-// (tile_shape / tile_passes >= 1), else the autotuned choice for this
-// problem, else, for a cold call of at most kTileMaxM iterations whose dual
-// is not kept (one pass, no dual in or out, so any storage type: where the
-// row-pipelined kernel measured faster than the tiles), a row-pipelined
-// shape when the problem fills the chip, else shape 0 and passes of about
-// kDefaultPassLen iterations.
-void pick_tiling(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, int n, int *shape, int *npass,
-                 bool single_cold_pass = false)
+// Duals a call reads before its first pass and leaves after its last, and
+// whether it can be followed by more iterations (then p^(s-1) is left too).
+struct CallDuals {
+    bool in, out, more;
+};
+
+// Estimated time of a call of n iterations as npass passes of one shape.
+double call_us(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, int n, int shape, int npass,
+               const CallDuals &cd)
 {
+    double t = 0.0;
+    for (int q = 0; q < npass; ++q) {
+        const int m = n / npass + (q < n % npass ? 1 : 0);
+        const bool first = q == 0, last = q == npass - 1;
+        const int pair = p.accel ? 4 : 2; // p and, with momentum, p_prev
+        const int io = 1 + (first ? (cd.in ? 2 : 0) : pair) + (!last || cd.more ? pair : cd.out ? 3 : 1); // 1: x, theta
+        t += tile_pass_us(ctx->num_cus, p.tv, shape, m, tile_units(shape, m, d.nx, d.ny) * d.B, (double)vol_elems(d), io);
+    }
+    return t;
+}
+
+// Tile shape and number of passes of the fused schedule: explicit
+// (tile_shape / tile_passes >= 1), else the autotuned choice for this problem,
+// else the pair with the smallest estimate of at most three passes more than
+// needed. Every choice gives the same bits with float32 duals. 16-bit duals
+// are rounded between passes, so their split is fixed: one pass for a cold
+// call of at most kTileMaxM iterations whose dual is not kept when the
+// row-pipelined shapes fill the chip, else passes of about kDefaultPassLen;
+// passes that touch a 16-bit dual run shape 0 whatever is chosen.
+void pick_tiling(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, int n, int *shape, int *npass,
+                 const CallDuals &cd)
+{
+    const int min_pass = (n + kTileMaxM - 1) / kTileMaxM;
+    const bool cold = !cd.in && !cd.out;
     *shape = 0;
     *npass = (n + kDefaultPassLen - 1) / kDefaultPassLen;
     auto it = ctx->tuned.find(tune_key(p, d));
     if (it != ctx->tuned.end()) {
         *shape = it->second.first;
         *npass = it->second.second;
-    } else if (single_cold_pass && tile_supported(p.tv) && n >= 1 && n <= kTileMaxM) {
+    } else if (tile_supported(p.tv) && !p.chambolle04 && n >= 1) {
+        int lo = min_pass, hi = std::min(n, min_pass + 2);
+        if (p.tile_passes >= 1) {
+            lo = hi = std::min(n, std::max(min_pass, p.tile_passes));
+        } else if (p.dual_dtype != SCI_DUAL_F32) {
+            lo = hi = cold && n <= kTileMaxM && default_row_shape(ctx, d, n) >= 0 ? 1 : std::max(min_pass, *npass);
+        }
+        const bool touches16 = p.dual_dtype != SCI_DUAL_F32 && (!cold || lo > 1);
+        double best = 0.0;
+        bool any = false;
+        for (int sh = 0; sh < tile_shape_count(); ++sh) {
+            if ((p.tile_shape >= 1 && sh != p.tile_shape - 1) || (touches16 && sh != 0 && p.tile_shape < 1)) continue;
+            for (int np = lo; np <= hi; ++np) {
+                const double t = call_us(ctx, p, d, n, sh, np, cd);
+                if (any && t >= best) continue;
+                any = true;
+                best = t;
+                *shape = sh;
+                *npass = np;
+            }
+        }
+    } else if (cold && tile_supported(p.tv) && n >= 1 && n <= kTileMaxM) { // Chambolle-2004: row-pipelined shapes
         const int rs = default_row_shape(ctx, d, n);
         if (rs >= 0) {
             *shape = rs;
@@ -235,21 +281,21 @@ void pick_tiling(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, 
     }
     if (p.tile_shape >= 1) *shape = p.tile_shape - 1;
     if (p.tile_passes >= 1) *npass = p.tile_passes;
-    const int min_pass = (n + kTileMaxM - 1) / kTileMaxM;
     if (*npass < min_pass) *npass = min_pass;
     if (*npass > n) *npass = n;
 }
 
 int fgp_tile_iterate(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const float *x, FgpRun &r, int n,
-                     float *theta, float *u_out, bool keep_dual, hipStream_t s, int force_shape, int force_passes)
+                     float *theta, float *u_out, bool keep_dual, hipStream_t s, int force_shape, int force_passes,
+                     bool more)
 {
     int shape = 0, npass = 1;
-    pick_tiling(ctx, p, d, n, &shape, &npass, !keep_dual && r.cur == nullptr);
+    if (force_shape < 0) pick_tiling(ctx, p, d, n, &shape, &npass, CallDuals{r.cur != nullptr, keep_dual, more});
     if (force_shape >= 0) shape = force_shape;
     if (force_passes >= 1) npass = force_passes;
     if (p.chambolle04 && p.tv != SCI_TV_VTV && !tile_shape_pipelined(shape)) { // only the row kernel has this step
         const int rs = default_row_shape(ctx, d, std::min(n, kTileMaxM));
-        shape = rs >= 0 ? rs : kTileShapes + 1;
+        shape = rs >= 0 ? rs : kFirstRowShape + 1;
     }
     // VTV projection passes hand their duals to the next pass of the call as
     // one record per voxel in the storage type (one load and one store instead
@@ -279,10 +325,15 @@ int fgp_tile_iterate(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, co
             bl = p.accel ? b : 0.0;
             tp.beta.b[t + 1] = (float)bl;
         }
-        void *pn = tp.quad_out ? r.quad[q & 1] : (!last || keep_dual) ? r.free_buffer() : nullptr;
-        // a one-iteration pass hands p^(s0) on as the next pass's p^(s-1);
-        // without acceleration no pass extrapolates, and p^(s-1) is not kept
-        void *ppn = (!tp.quad_out && (!last || keep_dual) && m > 1 && p.accel) ? r.free_buffer(pn) : nullptr;
+        void *pn = tp.quad_out                        ? r.quad[q & 1]
+                   : last && keep_dual && r.last_out ? r.last_out
+                   : !last || keep_dual              ? r.free_buffer()
+                                                     : nullptr;
+        // p^(s-1) is kept only where a later pass extrapolates from it: not
+        // after the last pass of a fixed-count call (the next call restarts
+        // the momentum) and not without acceleration; a one-iteration pass
+        // hands p^(s0) on as the next pass's p^(s-1)
+        void *ppn = (!tp.quad_out && (!last || (keep_dual && more)) && m > 1 && p.accel) ? r.free_buffer(pn) : nullptr;
         tp.pn_out = pn;
         tp.pp_out = ppn;
         tp.theta = last ? theta : nullptr;
@@ -379,14 +430,16 @@ int denoise_fixed(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const
             int shape = p.tile_shape >= 1 ? p.tile_shape - 1 : -1;
             if (shape < 0 || !tile_shape_pipelined(shape)) {
                 const int rs = default_row_shape(ctx, d, (n + npass - 1) / npass);
-                shape = rs >= 0 ? rs : kTileShapes + 1;
+                shape = rs >= 0 ? rs : kFirstRowShape + 1;
             }
             int H = 0, w = 0, c = 0;
             tile_shape_info(shape, &H, &w, &c);
             for (int q = 0; q < npass; ++q) {
                 const int m = n / npass + (q < n % npass ? 1 : 0);
                 const bool last = q == npass - 1;
-                float *out = (!last || keep_dual) ? (float *)r.free_buffer() : nullptr;
+                float *out = (float *)(last && keep_dual && r.last_out ? r.last_out
+                                       : !last || keep_dual            ? r.free_buffer()
+                                                                       : nullptr);
                 ProfScope prof(ctx, PF_FGP_FUSED, s);
                 int st = launch_clip_rows(H, m, d.nx, d.ny, d.B, x, (const float *)r.cur, out, alpha, p.lambda,
                                           last ? theta : nullptr, last ? u_out : nullptr, s);
@@ -399,7 +452,7 @@ int denoise_fixed(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const
             return SCI_OK;
         }
         for (int it = 0; it < p.n_inner; ++it) {
-            void *out = r.free_buffer();
+            void *out = it == p.n_inner - 1 && r.last_out ? r.last_out : r.free_buffer();
             ProfScope prof(ctx, PF_FGP_STREAM, s);
             int st = launch_clip(p.dual_dtype, d.nx, d.ny, d.B, x, r.cur, out, alpha, p.lambda, s);
             if (st != SCI_OK) return fail(ctx, st, "ATV-Clip pass");
@@ -782,8 +835,10 @@ int fgp_chunk(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &q, const flo
 {
     const bool fused = q.schedule != SCI_SCHED_STREAM && fused_supported(q, d);
     if (q.schedule == SCI_SCHED_FUSED && !fused) return fail(ctx, SCI_ERR_UNSUPPORTED, kFusedScope);
+    // the fewest passes with 16-bit duals, whose rounding depends on the split
     if (fused)
-        return fgp_tile_iterate(ctx, d, q, x, r, n, nullptr, nullptr, true, s, -1, (n + kTileMaxM - 1) / kTileMaxM);
+        return fgp_tile_iterate(ctx, d, q, x, r, n, nullptr, nullptr, true, s, -1,
+                                q.dual_dtype != SCI_DUAL_F32 ? (n + kTileMaxM - 1) / kTileMaxM : -1, true);
     return fgp_iterate(ctx, d, q, x, r, n, s);
 }
 
@@ -898,6 +953,7 @@ int sci_tv_denoise(sci_ctx *ctx, sci_dims d, const sci_tv_params *p, const float
     int status = SCI_OK;
     double gap = 0.0, primal = 0.0;
     if (!adaptive) {
+        r.last_out = dual_out; // the last pass stores the dual where the caller wants it
         if ((st = denoise_fixed(ctx, d, q, X_in, Theta_out, nullptr, dual_init, want_dual, r, stream)) != SCI_OK)
             return st;
         if (rel_gap_out) {
@@ -924,7 +980,7 @@ int sci_tv_denoise(sci_ctx *ctx, sci_dims d, const sci_tv_params *p, const float
         if (st == SCI_OK) st = check_launch(ctx, "k_tv_theta");
         if (st != SCI_OK) return st;
     }
-    if (dual_out) {
+    if (dual_out && r.cur != dual_out) {
         if (r.cur) launch_copy(r.cur, dual_out, db, stream);
         else launch_zero(dual_out, db, stream);
         if ((st = check_launch(ctx, "copy")) != SCI_OK) return st;
