@@ -135,6 +135,12 @@ int sci_create(sci_ctx **out, int device)
         delete ctx;
         return SCI_ERR_NOMEM;
     }
+    e = hipHostGetDevicePointer((void **)&ctx->dev_scalars, ctx->host_scalars, 0);
+    if (e != hipSuccess) {
+        (void)hipHostFree(ctx->host_scalars);
+        delete ctx;
+        return SCI_ERR_HIP;
+    }
     e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         (void)hipHostFree(ctx->host_scalars);

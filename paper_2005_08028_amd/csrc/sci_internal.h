@@ -62,7 +62,8 @@ struct sci_ctx {
     void *noalloc_scratch = nullptr; // device address of the fixed scratch array (sci_gap_tv_noalloc)
     std::string last_error;
     sci::Buf ws[sci::WS_COUNT];
-    double *host_scalars = nullptr; // pinned, 8 doubles
+    double *host_scalars = nullptr; // pinned, 8 doubles; reductions store here
+    double *dev_scalars = nullptr;  // the same memory as the device addresses it
     hipStream_t capture_stream = nullptr;
     std::map<std::string, sci::GraphEntry> graphs;
     // profiler: event pairs around launches (not recorded while capturing)
@@ -224,18 +225,19 @@ int launch_fgp_tile(int tv, int dual_dtype, int m, int shape, int nx, int ny, in
                     const TilePass &tp, float lam, hipStream_t s, bool chambolle04 = false);
 
 // ---- launchers (k_reduce.hip) -------------------------------------------------
-// Deterministic two-stage FP64 reductions into out_dev (device doubles).
+// Deterministic two-stage FP64 reductions into out (device-addressable
+// doubles, e.g. sci_ctx::dev_scalars).
 int reduce_partial_blocks();
 size_t gap_partial_doubles(int nx, int ny, int B, int tv);
-// out_dev[0] = max_ij sum_k C_kij^2 (partials: reduce_partial_blocks() entries)
-void launch_max_s(int nx, int ny, int B, const float *C, double *partials, double *out_dev, hipStream_t s);
-void launch_sqdiff(int64_t n, const float *a, const float *b, double *partials, double *out_dev, hipStream_t s);
+// out[0] = max_ij sum_k C_kij^2 (partials: reduce_partial_blocks() entries)
+void launch_max_s(int nx, int ny, int B, const float *C, double *partials, double *out, hipStream_t s);
+void launch_sqdiff(int64_t n, const float *a, const float *b, double *partials, double *out, hipStream_t s);
 void launch_residual_sq(int nx, int ny, int B, const float *C, const float *X, const float *Y, double *partials,
-                        double *out_dev, hipStream_t s);
-// out_dev[0] = TV(theta), out_dev[1] = <D theta, p>, out_dev[2] = ||theta - x||^2;
+                        double *out, hipStream_t s);
+// out[0] = TV(theta), out[1] = <D theta, p>, out[2] = ||theta - x||^2;
 // `partials` holds gap_partial_doubles(nx, ny, B, tv) doubles. VTV with
 // B > 48: SCI_ERR_UNSUPPORTED, nothing launched.
 int launch_gap_terms(int tv, int dual_dtype, int nx, int ny, int B, float lam, const float *x, const void *p,
-                     double *partials, double *out_dev, hipStream_t s);
+                     double *partials, double *out, hipStream_t s);
 
 } // namespace sci

@@ -482,30 +482,34 @@ int denoise_fixed(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &p, const
     return check_launch(ctx, "k_tv_theta");
 }
 
+// Waits for the reductions queued on s, whose results are then in
+// ctx->host_scalars.
+int wait_scalars(sci_ctx *ctx, hipStream_t s)
+{
+    hipError_t e = hipStreamSynchronize(s);
+    return e == hipSuccess ? SCI_OK : fail_hip(ctx, e, "hipStreamSynchronize");
+}
+
 // Relative duality gap lambda (TV - <D theta, p>) / P(theta) of the dual p,
 // computed in FP64 on the GPU and read back (synchronises the stream).
 int rel_gap(sci_ctx *ctx, const sci_dims &d, int tv, int dual_dtype, float lam, const float *x, const void *p,
             double *gap, double *primal, hipStream_t s)
 {
     const size_t np = gap_partial_doubles(d.nx, d.ny, d.B, tv);
-    int st = ensure_ws(ctx, WS_PARTIAL, (np + 8) * sizeof(double), s);
+    int st = ensure_ws(ctx, WS_PARTIAL, np * sizeof(double), s);
     if (st != SCI_OK) return st;
     double *part = (double *)ctx->ws[WS_PARTIAL].ptr;
-    double *outd = part + np;
     if (!p) {
         st = ensure_ws(ctx, WS_DUAL2, 2 * vol_elems(d) * dual_elem_bytes(dual_dtype), s);
         if (st != SCI_OK) return st;
         launch_zero(ctx->ws[WS_DUAL2].ptr, 2 * vol_elems(d) * dual_elem_bytes(dual_dtype), s);
         p = ctx->ws[WS_DUAL2].ptr;
     }
-    st = launch_gap_terms(tv, dual_dtype, d.nx, d.ny, d.B, lam, x, p, part, outd, s);
+    st = launch_gap_terms(tv, dual_dtype, d.nx, d.ny, d.B, lam, x, p, part, ctx->dev_scalars, s);
     if (st != SCI_OK) return fail(ctx, st, "duality gap: VTV supports B <= 48 frames");
     st = check_launch(ctx, "k_gap_rows");
     if (st != SCI_OK) return st;
-    hipError_t e = hipMemcpyAsync(ctx->host_scalars, outd, 3 * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipMemcpyAsync");
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipStreamSynchronize");
+    if ((st = wait_scalars(ctx, s)) != SCI_OK) return st;
     const double tvv = ctx->host_scalars[0], inner = ctx->host_scalars[1], fid = ctx->host_scalars[2];
     *gap = (double)lam * (tvv - inner);
     *primal = 0.5 * fid + (double)lam * tvv;
@@ -689,15 +693,6 @@ int run_outer(sci_ctx *ctx, const sci_dims &d, const sci_solver_params *p, const
     return SCI_OK;
 }
 
-int read_scalars(sci_ctx *ctx, const double *dev, int n, hipStream_t s)
-{
-    hipError_t e = hipMemcpyAsync(ctx->host_scalars, dev, n * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipMemcpyAsync");
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail_hip(ctx, e, "hipStreamSynchronize");
-    return SCI_OK;
-}
-
 // L(f) = max_ij S_ij, the largest eigenvalue of Phi^T Phi (read back; synchronises).
 int lipschitz(sci_ctx *ctx, const sci_dims &d, const float *C, double *L, hipStream_t s)
 {
@@ -705,10 +700,9 @@ int lipschitz(sci_ctx *ctx, const sci_dims &d, const float *C, double *L, hipStr
     int st = ensure_ws(ctx, WS_PARTIAL, (3 * (size_t)nb + 8) * sizeof(double), s);
     if (st != SCI_OK) return st;
     double *part = (double *)ctx->ws[WS_PARTIAL].ptr;
-    double *outd = part + 3 * nb;
-    launch_max_s(d.nx, d.ny, d.B, C, part, outd, s);
+    launch_max_s(d.nx, d.ny, d.B, C, part, ctx->dev_scalars, s);
     if ((st = check_launch(ctx, "k_max_s")) != SCI_OK) return st;
-    if ((st = read_scalars(ctx, outd, 1, s)) != SCI_OK) return st;
+    if ((st = wait_scalars(ctx, s)) != SCI_OK) return st;
     *L = ctx->host_scalars[0];
     return SCI_OK;
 }
@@ -1238,9 +1232,9 @@ int sci_psnr(sci_ctx *ctx, int64_t count, const float *a, const float *ref, doub
     const int nb = reduce_partial_blocks();
     if ((st = ensure_ws(ctx, WS_PARTIAL, (3 * (size_t)nb + 8) * sizeof(double), stream)) != SCI_OK) return st;
     double *part = (double *)ctx->ws[WS_PARTIAL].ptr;
-    launch_sqdiff(count, a, ref, part, part + 3 * nb, stream);
+    launch_sqdiff(count, a, ref, part, ctx->dev_scalars, stream);
     if ((st = check_launch(ctx, "k_sqdiff")) != SCI_OK) return st;
-    if ((st = read_scalars(ctx, part + 3 * nb, 1, stream)) != SCI_OK) return st;
+    if ((st = wait_scalars(ctx, stream)) != SCI_OK) return st;
     const double mse = ctx->host_scalars[0] / (double)count;
     *out_host = 10.0 * std::log10(peak * peak / mse);
     return SCI_OK;
@@ -1257,9 +1251,9 @@ int sci_residual_sq(sci_ctx *ctx, sci_dims d, const float *C, const float *X, co
     const int nb = reduce_partial_blocks();
     if ((st = ensure_ws(ctx, WS_PARTIAL, (3 * (size_t)nb + 8) * sizeof(double), stream)) != SCI_OK) return st;
     double *part = (double *)ctx->ws[WS_PARTIAL].ptr;
-    launch_residual_sq(d.nx, d.ny, d.B, C, X, Y, part, part + 3 * nb, stream);
+    launch_residual_sq(d.nx, d.ny, d.B, C, X, Y, part, ctx->dev_scalars, stream);
     if ((st = check_launch(ctx, "k_resid")) != SCI_OK) return st;
-    if ((st = read_scalars(ctx, part + 3 * nb, 1, stream)) != SCI_OK) return st;
+    if ((st = wait_scalars(ctx, stream)) != SCI_OK) return st;
     *out_host = ctx->host_scalars[0];
     return SCI_OK;
 }
