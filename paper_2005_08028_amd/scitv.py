@@ -117,8 +117,15 @@ lib = load_library()
 
 # ---- marshalling helpers ------------------------------------------------------
 
+# The raw handle of the current device's current stream, without building the
+# Stream object that torch.cuda.current_stream() returns (where torch has it).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -134,9 +141,9 @@ def _dev(t: Optional[torch.Tensor], dtype=torch.float32, shape=None, name="tenso
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:  # a torch.Size compares with any tuple
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check(ctx, status: int, allow=(SCI_OK,)):
@@ -148,9 +155,10 @@ def _check(ctx, status: int, allow=(SCI_OK,)):
 
 
 def _dims(vol: torch.Tensor) -> sci_dims:
-    if vol.dim() != 3:
+    shape = vol.shape
+    if len(shape) != 3:
         raise ValueError("video tensors are [B][nx][ny]")
-    B, nx, ny = vol.shape
+    B, nx, ny = shape
     return sci_dims(nx, ny, B)
 
 
