@@ -6,6 +6,8 @@
 // over the B frames. The per-pixel sum over frames stays in a register.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sci_internal.h"
 #include "sci_math.h"
 
@@ -60,6 +62,65 @@ __global__ __launch_bounds__(kBlock) void k_weights(uint32_t npix, int B, const 
     Sinv[pix] = s > 0.0f ? 1.0f / s : 0.0f;
 }
 
+// A solve's setup in one pass over the masks: Sinv = 1 / (sum_k C_k^2 + rho)
+// (nullable), theta = Phi^T Y (nullable), u = 0 (nullable), the masks packed
+// one bit per frame, and one flag per kProjBlock pixels: 1 when all their
+// entries are 0 or 1, else 0 (the projection of that block then reads C). All
+// masks of a pixel are loaded before their first use, into KB >= B registers.
+// A memory stream with a launch's latency under it. Weights, packing, a global
+// flag, theta and u as kernels of their own read C three times; with the copy
+// of theta that ends a solve of no iterations, 10.8 -> 5.8 us at 256x256x8,
+// 25.4 -> 17.7 us at 512x512x16, 126 -> 88 us at 1024x1024x24. The plain
+// forward and adjoint products gain nothing from the same form (2.4 -> 2.0 and
+// 2.6 -> 2.8 us at 256x256x8, 36.4 -> 37.6 and 44.5 -> 47.5 at 1024x1024x24).
+template <int KB>
+__global__ __launch_bounds__(kProjBlock) void k_setup_reg(uint32_t npix, int B, const float *__restrict__ C,
+                                                          const float *__restrict__ Y, float rho,
+                                                          float *__restrict__ Sinv, float *__restrict__ theta,
+                                                          float *__restrict__ u, uint32_t *__restrict__ bits,
+                                                          int *__restrict__ flags)
+{
+    const int block = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+    const uint32_t pix = (uint32_t)block * kProjBlock + threadIdx.x;
+    bool binary = true;
+    if (pix < npix) {
+        float c[KB];
+#pragma unroll
+        for (int k = 0; k < KB; ++k) c[k] = C[(uint32_t)min(k, B - 1) * npix + pix];
+        const float y = theta ? Y[pix] : 0.0f;
+        float s = 0.0f;
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            if (k >= B) continue;
+            const uint32_t o = (uint32_t)k * npix + pix;
+            s = fmaf(c[k], c[k], s);
+            if (c[k] == 1.0f) m |= 1u << k;
+            else if (c[k] != 0.0f) binary = false;
+            if (theta) theta[o] = c[k] * y;
+            if (u) u[o] = 0.0f;
+        }
+        s = s + rho;
+        if (Sinv) Sinv[pix] = s > 0.0f ? 1.0f / s : 0.0f;
+        bits[pix] = m;
+    }
+    const bool all = __all(binary);
+    if (threadIdx.x == 0) flags[block] = all ? 1 : 0;
+}
+
+// Calls f(integral_constant<int, KB>) with the smallest even KB that holds B frames (B <= 32).
+template <int KB = 2, typename F> void with_slots(int B, F &&f)
+{
+    if constexpr (KB < 32) {
+        if (B > KB) {
+            with_slots<KB + 2>(B, f);
+            return;
+        }
+    }
+    f(std::integral_constant<int, KB>{});
+}
+inline dim3 proj_grid(uint32_t npix) { return dim3((npix + kProjBlock - 1) / kProjBlock); }
+
 // Projection modes: what the kernels take as v, the point they project.
 //   kProjGap    v = theta (Eq. (21))
 //   kProjAdmm   v = theta - u (Eq. (24)); the kernel also writes the denoiser
@@ -112,27 +173,6 @@ __global__ __launch_bounds__(kBlock) void k_project(uint32_t npix, int B, float 
     }
 }
 
-// Binary masks packed one bit per frame into a 32-bit word per pixel
-// (B <= 32): bits[pix] bit k = (C_k(pix) == 1). flag (set to 1 beforehand)
-// is cleared when any entry is neither 0 nor 1; the projection then reads C.
-__global__ __launch_bounds__(kBlock) void k_pack_masks(uint32_t npix, int B, const float *__restrict__ C,
-                                                       uint32_t *__restrict__ bits, int *__restrict__ flag)
-{
-    const uint32_t pix = blockIdx.x * kBlock + threadIdx.x;
-    if (pix >= npix) return;
-    uint32_t b = 0u;
-    bool ok = true;
-    for (int k = 0; k < B; ++k) {
-        const float c = C[(uint32_t)k * npix + pix];
-        if (c == 1.0f) b |= 1u << k;
-        else if (c != 0.0f) ok = false;
-    }
-    bits[pix] = b;
-    if (!ok) atomicAnd(flag, 0);
-}
-
-__global__ void k_set_flag(int *flag, int v) { *flag = v; }
-
 // The projection with every frame of a pixel in registers (B <= KB <= 32), so
 // that each volume is read once. HBM stream (GAP: read theta, write x); below
 // a few million voxels its time is the latency of its loads. All of them are
@@ -150,21 +190,22 @@ __global__ void k_set_flag(int *flag, int v) { *flag = v; }
 // theta the row-major denoisers (VTV) left in its L2: 8.6 -> 5.8 us at
 // 512x512x10.
 //
-// Binary masks come as packed bits (*flag != 0): C_k is 0 or 1, so
-// fmaf(C_k, v, acc) and fmaf(C_k, r, v) give the same values as with the float
-// masks, which are read where *flag is 0.
+// Binary masks come as packed bits (flags[block] != 0, see k_setup_reg): C_k is
+// 0 or 1, so fmaf(C_k, v, acc) and fmaf(C_k, r, v) give the same values as with
+// the float masks, which are read where the block's flag is 0.
 template <int MODE, int KB>
 __global__ __launch_bounds__(kProjBlock) void k_project_reg(uint32_t npix, int B, float ex, float a1, float a2,
                                                             const float *__restrict__ w,
                                                             const float *__restrict__ theta,
                                                             const float *__restrict__ u, const float *__restrict__ C,
                                                             const uint32_t *__restrict__ bits,
-                                                            const int *__restrict__ flag,
+                                                            const int *__restrict__ flags,
                                                             const float *__restrict__ Y,
                                                             const float *__restrict__ Sinv, float *__restrict__ x,
                                                             float *__restrict__ svol)
 {
-    const uint32_t pix = (uint32_t)xcd_contiguous((int)blockIdx.x, (int)gridDim.x) * kProjBlock + threadIdx.x;
+    const int block = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+    const uint32_t pix = (uint32_t)block * kProjBlock + threadIdx.x;
     if (pix >= npix) return;
     constexpr bool ADMM = MODE == kProjAdmm;
     float v[KB], uu[KB], ww[KB];
@@ -199,7 +240,7 @@ __global__ __launch_bounds__(kProjBlock) void k_project_reg(uint32_t npix, int B
             }
         }
     };
-    if (*flag != 0) { // uniform
+    if (flags[block] != 0) { // uniform over the workgroup
         finish([&](int k) { return (m >> k) & 1u ? 1.0f : 0.0f; });
     } else {
         float c[KB];
@@ -215,32 +256,29 @@ struct ProjArgs {
     float ex, a1, a2;
     const float *w, *theta, *u, *C;
     const uint32_t *bits;
-    const int *flag;
+    const int *flags;
     const float *Y, *Sinv;
     float *x, *svol;
     hipStream_t s;
 };
 
-// Launch with the smallest even slot count that holds B frames.
-template <int MODE, int KB = 2> void launch_project_reg(const ProjArgs &a)
+template <int MODE> void launch_project_reg(const ProjArgs &a)
 {
-    if constexpr (KB < 32) {
-        if (a.B > KB) return launch_project_reg<MODE, KB + 2>(a);
-    }
-    hipLaunchKernelGGL((k_project_reg<MODE, KB>), dim3((a.npix + kProjBlock - 1) / kProjBlock), dim3(kProjBlock), 0, a.s,
-                       a.npix, a.B, a.ex, a.a1, a.a2, a.w, a.theta, a.u, a.C, a.bits, a.flag, a.Y, a.Sinv, a.x,
-                       a.svol);
+    with_slots(a.B, [&](auto kb) {
+        hipLaunchKernelGGL((k_project_reg<MODE, decltype(kb)::value>), proj_grid(a.npix), dim3(kProjBlock), 0, a.s, a.npix,
+                           a.B, a.ex, a.a1, a.a2, a.w, a.theta, a.u, a.C, a.bits, a.flags, a.Y, a.Sinv, a.x, a.svol);
+    });
 }
 
-// At most 32 frames, packed masks at hand (every solver has them): registers;
-// else, frames beyond the mask word, the loop over frames.
+// At most 32 frames, as many as a mask word has bits: registers; beyond, the
+// loop over frames.
 template <int MODE>
 void launch_project(uint32_t npix, int B, float ex, const float *theta, const float *u, const float *C,
                     const float *Y, const float *Sinv, float *x, float *svol, hipStream_t s, const uint32_t *cbits,
-                    const int *cflag, float a1 = 0.0f, float a2 = 0.0f, const float *w = nullptr)
+                    const int *cflags, float a1 = 0.0f, float a2 = 0.0f, const float *w = nullptr)
 {
-    if (B <= 32 && cbits && cflag)
-        launch_project_reg<MODE>(ProjArgs{npix, B, ex, a1, a2, w, theta, u, C, cbits, cflag, Y, Sinv, x, svol, s});
+    if (B <= 32)
+        launch_project_reg<MODE>(ProjArgs{npix, B, ex, a1, a2, w, theta, u, C, cbits, cflags, Y, Sinv, x, svol, s});
     else
         hipLaunchKernelGGL((k_project<MODE>), dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, ex, a1, a2, w, theta,
                            u, C, Y, Sinv, x, svol);
@@ -331,46 +369,51 @@ void launch_adjoint(int nx, int ny, int B, const float *C, const float *Y, float
     hipLaunchKernelGGL(k_adjoint, dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, C, Y, X);
 }
 
-void launch_weights(int nx, int ny, int B, const float *C, float rho, float *Sinv, hipStream_t s)
+size_t mask_flags_count(size_t npix) { return (npix + kProjBlock - 1) / kProjBlock; }
+
+void launch_setup(int nx, int ny, int B, const float *C, const float *Y, float rho, float *Sinv, float *theta, float *u,
+                  uint32_t *bits, int *flags, hipStream_t s)
 {
-    uint32_t npix = (uint32_t)nx * (uint32_t)ny;
-    hipLaunchKernelGGL(k_weights, dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, C, rho, Sinv);
+    const uint32_t npix = (uint32_t)nx * (uint32_t)ny;
+    if (B > 32) { // no packed masks: the projection loops over the frames
+        if (Sinv) hipLaunchKernelGGL(k_weights, dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, C, rho, Sinv);
+        if (theta) launch_adjoint(nx, ny, B, C, Y, theta, s);
+        if (u) launch_zero(u, (size_t)npix * B * sizeof(float), s);
+        return;
+    }
+    with_slots(B, [&](auto kb) {
+        hipLaunchKernelGGL(k_setup_reg<decltype(kb)::value>, proj_grid(npix), dim3(kProjBlock), 0, s, npix, B, C, Y, rho,
+                           Sinv, theta, u, bits, flags);
+    });
 }
 
 void launch_gap_project(int nx, int ny, int B, const float *theta, const float *C, const float *Y,
-                        const float *Sinv, float *x, hipStream_t s, const uint32_t *cbits, const int *cflag)
+                        const float *Sinv, float *x, hipStream_t s, const uint32_t *cbits, const int *cflags)
 {
     launch_project<kProjGap>((uint32_t)nx * (uint32_t)ny, B, 0.0f, theta, nullptr, C, Y, Sinv, x, nullptr, s, cbits,
-                             cflag);
+                             cflags);
 }
 
 void launch_admm_project(int nx, int ny, int B, const float *theta, const float *u, const float *C,
                          const float *Y, const float *Sinv, float *x, float *svol, hipStream_t s,
-                         const uint32_t *cbits, const int *cflag)
+                         const uint32_t *cbits, const int *cflags)
 {
-    launch_project<kProjAdmm>((uint32_t)nx * (uint32_t)ny, B, 0.0f, theta, u, C, Y, Sinv, x, svol, s, cbits, cflag);
+    launch_project<kProjAdmm>((uint32_t)nx * (uint32_t)ny, B, 0.0f, theta, u, C, Y, Sinv, x, svol, s, cbits, cflags);
 }
 
 void launch_fista_project(int nx, int ny, int B, const float *x, const float *x_prev, float ex, const float *C,
                           const float *Y, const float *W, float *z, hipStream_t s, const uint32_t *cbits,
-                          const int *cflag)
+                          const int *cflags)
 {
-    launch_project<kProjFista>((uint32_t)nx * (uint32_t)ny, B, ex, x, x_prev, C, Y, W, z, nullptr, s, cbits, cflag);
+    launch_project<kProjFista>((uint32_t)nx * (uint32_t)ny, B, ex, x, x_prev, C, Y, W, z, nullptr, s, cbits, cflags);
 }
 
 void launch_twist_project(int nx, int ny, int B, const float *x, const float *x_prev, const float *theta, float a0,
                           float a1, float a2, const float *C, const float *Y, const float *W, float *z, float *x_next,
-                          hipStream_t s, const uint32_t *cbits, const int *cflag)
+                          hipStream_t s, const uint32_t *cbits, const int *cflags)
 {
-    launch_project<kProjTwist>((uint32_t)nx * (uint32_t)ny, B, a0, x, x_prev, C, Y, W, z, x_next, s, cbits, cflag, a1,
+    launch_project<kProjTwist>((uint32_t)nx * (uint32_t)ny, B, a0, x, x_prev, C, Y, W, z, x_next, s, cbits, cflags, a1,
                                a2, theta);
-}
-
-void launch_pack_masks(int nx, int ny, int B, const float *C, uint32_t *bits, int *flag, hipStream_t s)
-{
-    const uint32_t npix = (uint32_t)nx * (uint32_t)ny;
-    hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(1), 0, s, flag, B <= 32 ? 1 : 0);
-    if (B <= 32) hipLaunchKernelGGL(k_pack_masks, dim3(grid_for(npix)), dim3(kBlock), 0, s, npix, B, C, bits, flag);
 }
 
 // Device-to-device copy and zero fill as plain kernels, so that they can be

@@ -80,11 +80,12 @@ namespace sci {
 
 // ---- fixed scratch of the allocation-free GAP entry point (noalloc.hip) -----
 // Layout: 1 / S image (float per pixel), packed masks (32-bit word per
-// pixel), the packed-mask flag; sized for nx * ny <= kNoAllocMaxPixels.
+// pixel), the packed-mask flags (one per 64 pixels); sized for
+// nx * ny <= kNoAllocMaxPixels.
 constexpr size_t kNoAllocMaxPixels = (size_t)1 << 22;
 constexpr size_t kNoAllocBitsOffset = kNoAllocMaxPixels * 4;
 constexpr size_t kNoAllocFlagOffset = kNoAllocBitsOffset + kNoAllocMaxPixels * 4;
-constexpr size_t kNoAllocScratchBytes = kNoAllocFlagOffset + 256;
+constexpr size_t kNoAllocScratchBytes = kNoAllocFlagOffset + kNoAllocMaxPixels / 64 * 4;
 // Device address of the array on `device`, which must be current; looked up
 // once per device and cached. SCI_OK or SCI_ERR_HIP.
 int noalloc_scratch_lookup(int device, void **addr);
@@ -113,32 +114,35 @@ class ProfScope {
 // ---- launchers (k_sensing.hip) ------------------------------------------------
 void launch_forward(int nx, int ny, int B, const float *C, const float *X, float *Y, hipStream_t s);
 void launch_adjoint(int nx, int ny, int B, const float *C, const float *Y, float *X, hipStream_t s);
-void launch_weights(int nx, int ny, int B, const float *C, float rho, float *Sinv, hipStream_t s);
+// Setup of a solve: Sinv = 1 / (sum_k C_k^2 + rho), theta = Phi^T Y, u = 0 (each
+// nullable), and for B <= 32 the masks packed one bit per frame with a flag
+// per 64 pixels (mask_flags_count of them; 1: every entry is 0 or 1). All on
+// the device: graph-capturable.
+void launch_setup(int nx, int ny, int B, const float *C, const float *Y, float rho, float *Sinv, float *theta, float *u,
+                  uint32_t *bits, int *flags, hipStream_t s);
+size_t mask_flags_count(size_t npix);
 // x = theta + C .* ((Y - sum_k C_k theta_k) .* Sinv)
-// GAP / ADMM projection. cbits / cflag (nullable): masks packed by
-// launch_pack_masks; when *cflag is 1 the kernel reads the bits instead of C.
+// GAP / ADMM projection. cbits / cflags: masks packed by launch_setup; where a
+// flag is 1 the kernel reads the bits instead of C.
 void launch_gap_project(int nx, int ny, int B, const float *theta, const float *C, const float *Y,
-                        const float *Sinv, float *x, hipStream_t s, const uint32_t *cbits = nullptr,
-                        const int *cflag = nullptr);
+                        const float *Sinv, float *x, hipStream_t s, const uint32_t *cbits,
+                        const int *cflags);
 // v = theta - u; x = v + C .* ((Y - sum_k C_k v_k) .* Sinv); s = u + x
 // (x nullable: then only s is stored)
 void launch_admm_project(int nx, int ny, int B, const float *theta, const float *u, const float *C,
                          const float *Y, const float *Sinv, float *x, float *svol, hipStream_t s,
-                         const uint32_t *cbits = nullptr, const int *cflag = nullptr);
+                         const uint32_t *cbits, const int *cflags);
 // FISTA gradient step from the extrapolated point formed on load:
 // v = x + ex (x - x_prev), z = v + C .* ((Y - sum_k C_k v_k) .* W)
 void launch_fista_project(int nx, int ny, int B, const float *x, const float *x_prev, float ex, const float *C,
-                          const float *Y, const float *W, float *z, hipStream_t s, const uint32_t *cbits = nullptr,
-                          const int *cflag = nullptr);
+                          const float *Y, const float *W, float *z, hipStream_t s, const uint32_t *cbits,
+                          const int *cflags);
 // TwIST: the two-step update x_next = a0 x_prev + a1 x + a2 theta formed on
 // load and stored (x_next must not overlap any input), then
 // z = x_next + C .* ((Y - sum_k C_k x_next_k) .* W)
 void launch_twist_project(int nx, int ny, int B, const float *x, const float *x_prev, const float *theta, float a0,
                           float a1, float a2, const float *C, const float *Y, const float *W, float *z, float *x_next,
-                          hipStream_t s, const uint32_t *cbits = nullptr, const int *cflag = nullptr);
-// bits[pix] bit k = (C_k(pix) == 1); *flag = 1 when every entry of C is 0 or 1
-// and B <= 32, else 0 (all on the device: graph-capturable).
-void launch_pack_masks(int nx, int ny, int B, const float *C, uint32_t *bits, int *flag, hipStream_t s);
+                          hipStream_t s, const uint32_t *cbits, const int *cflags);
 void launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 void launch_fill(float *dst, float v, size_t n, hipStream_t s);
 // theta = x + c (x - xp)

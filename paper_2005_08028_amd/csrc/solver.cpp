@@ -518,10 +518,13 @@ int rel_gap(sci_ctx *ctx, const sci_dims &d, int tv, int dual_dtype, float lam, 
 
 // ---- outer loops ---------------------------------------------------------------
 
-// Scratch for the packed masks: one 32-bit word per pixel, then the flag.
-size_t cbits_bytes(const sci_dims &d) { return ((img_elems(d) * sizeof(uint32_t) + 255) & ~(size_t)255) + 256; }
+// Scratch for the packed masks: one 32-bit word per pixel, then the flags.
+size_t cbits_bytes(const sci_dims &d)
+{
+    return ((img_elems(d) * sizeof(uint32_t) + 255) & ~(size_t)255) + mask_flags_count(img_elems(d)) * sizeof(int);
+}
 uint32_t *cbits_ptr(sci_ctx *ctx) { return (uint32_t *)ctx->ws[WS_CBITS].ptr; }
-int *cflag_ptr(sci_ctx *ctx, const sci_dims &d)
+int *cflags_ptr(sci_ctx *ctx, const sci_dims &d)
 {
     return (int *)((char *)ctx->ws[WS_CBITS].ptr + ((img_elems(d) * sizeof(uint32_t) + 255) & ~(size_t)255));
 }
@@ -537,7 +540,7 @@ struct OuterArgs {
     bool admm;
     float *Sinv;               // 1 / (S + rho) image
     uint32_t *cbits;           // packed masks, one word per pixel
-    int *cflag;                // 1 when the packed masks apply
+    int *cflags;               // per 64 pixels: 1 when the packed masks apply
     float *svol, *u;           // ADMM only
     void *duals[4];            // dual fields (nullptr: none needed)
     void *quads[2];            // VTV dual records between passes (nullptr: not used)
@@ -553,15 +556,14 @@ int enqueue_outer(sci_ctx *ctx, const OuterArgs &a, hipStream_t s)
     float *svol = a.admm ? a.svol : nullptr;
     float *u = a.admm ? a.u : nullptr;
     uint32_t *cbits = a.cbits;
-    int *cflag = a.cflag;
+    int *cflags = a.cflags;
 
     {
         ProfScope prof(ctx, PF_SETUP, s);
-        launch_weights(d.nx, d.ny, d.B, a.C, a.admm ? a.p.rho : 0.0f, Sinv, s);
-        launch_pack_masks(d.nx, d.ny, d.B, a.C, cbits, cflag, s);
-        if (a.X_init) launch_copy(a.X_init, theta, vb, s);     // theta^(0) = X_init
-        else launch_adjoint(d.nx, d.ny, d.B, a.C, a.Y, theta, s); // theta^(0) = Phi^T y
-        if (a.admm) launch_zero(u, vb, s);                     // u^(0) = 0
+        // theta^(0) = Phi^T y (or X_init), u^(0) = 0
+        launch_setup(d.nx, d.ny, d.B, a.C, a.Y, a.admm ? a.p.rho : 0.0f, Sinv, a.X_init ? nullptr : theta, u, cbits,
+                     cflags, s);
+        if (a.X_init) launch_copy(a.X_init, theta, vb, s);
     }
     int st = check_launch(ctx, "outer setup");
     if (st != SCI_OK) return st;
@@ -579,7 +581,7 @@ int enqueue_outer(sci_ctx *ctx, const OuterArgs &a, hipStream_t s)
         if (!a.admm) {
             {
                 ProfScope prof(ctx, PF_PROJECT, s);
-                launch_gap_project(d.nx, d.ny, d.B, theta, a.C, a.Y, Sinv, a.X_out, s, cbits, cflag);
+                launch_gap_project(d.nx, d.ny, d.B, theta, a.C, a.Y, Sinv, a.X_out, s, cbits, cflags);
             }
             st = check_launch(ctx, "k_project");
             if (st != SCI_OK) return st;
@@ -590,7 +592,7 @@ int enqueue_outer(sci_ctx *ctx, const OuterArgs &a, hipStream_t s)
                 // forms u = s - theta itself, so x is stored on the last pass only
                 float *x = t + 1 == a.p.outer_iters ? a.X_out : nullptr;
                 ProfScope prof(ctx, PF_PROJECT, s);
-                launch_admm_project(d.nx, d.ny, d.B, theta, u, a.C, a.Y, Sinv, x, svol, s, cbits, cflag);
+                launch_admm_project(d.nx, d.ny, d.B, theta, u, a.C, a.Y, Sinv, x, svol, s, cbits, cflags);
             }
             st = check_launch(ctx, "k_project");
             if (st != SCI_OK) return st;
@@ -654,7 +656,7 @@ int run_outer(sci_ctx *ctx, const sci_dims &d, const sci_solver_params *p, const
     if ((st = ensure_ws(ctx, WS_CBITS, cbits_bytes(d), s)) != SCI_OK) return st;
 
     OuterArgs a{d, *p, Y, C, X_init, X_out, Theta_out ? Theta_out : (float *)ctx->ws[WS_THETA].ptr, admm,
-                (float *)ctx->ws[WS_SINV].ptr, cbits_ptr(ctx), cflag_ptr(ctx, d),
+                (float *)ctx->ws[WS_SINV].ptr, cbits_ptr(ctx), cflags_ptr(ctx, d),
                 admm ? (float *)ctx->ws[WS_SVOL].ptr : nullptr, admm ? (float *)ctx->ws[WS_UVOL].ptr : nullptr,
                 {nullptr, nullptr, nullptr, nullptr}, {nullptr, nullptr}, 0};
     for (int k = 0; k < 4; ++k) a.duals[k] = ctx->ws[WS_DUAL0 + k].ptr;
@@ -762,9 +764,9 @@ int run_prox_grad(sci_ctx *ctx, const sci_dims &d, const sci_solver_params *p, c
     {
         ProfScope prof(ctx, PF_SETUP, s);
         launch_fill(W, (float)(1.0 / L), img_elems(d), s);
-        launch_pack_masks(d.nx, d.ny, d.B, C, cbits_ptr(ctx), cflag_ptr(ctx, d), s);
-        if (X_init) launch_copy(X_init, xa, vb, s); // x^(0)
-        else launch_adjoint(d.nx, d.ny, d.B, C, Y, xa, s);
+        launch_setup(d.nx, d.ny, d.B, C, Y, 0.0f, nullptr, X_init ? nullptr : xa, nullptr, cbits_ptr(ctx),
+                     cflags_ptr(ctx, d), s); // x^(0) = Phi^T y (or X_init)
+        if (X_init) launch_copy(X_init, xa, vb, s);
         launch_copy(xa, theta, vb, s);
     }
     if ((st = check_launch(ctx, "setup")) != SCI_OK) return st;
@@ -781,14 +783,14 @@ int run_prox_grad(sci_ctx *ctx, const sci_dims &d, const sci_solver_params *p, c
             // FISTA steps from the extrapolated point (x^(0) itself at first),
             // TwIST from x^(t), formed here (into the third buffer) once t >= 2
             if (!twist && t > 0) {
-                launch_fista_project(d.nx, d.ny, d.B, xa, xb, ex, C, Y, W, z, s, cbits_ptr(ctx), cflag_ptr(ctx, d));
+                launch_fista_project(d.nx, d.ny, d.B, xa, xb, ex, C, Y, W, z, s, cbits_ptr(ctx), cflags_ptr(ctx, d));
             } else if (pend) {
                 launch_twist_project(d.nx, d.ny, d.B, xa, xb, theta, a0, a1, a2, C, Y, W, z, xc, s, cbits_ptr(ctx),
-                                     cflag_ptr(ctx, d));
+                                     cflags_ptr(ctx, d));
                 rotate();
                 pend = false;
             } else {
-                launch_gap_project(d.nx, d.ny, d.B, xa, C, Y, W, z, s, cbits_ptr(ctx), cflag_ptr(ctx, d));
+                launch_gap_project(d.nx, d.ny, d.B, xa, C, Y, W, z, s, cbits_ptr(ctx), cflags_ptr(ctx, d));
             }
         }
         if ((st = check_launch(ctx, "k_project")) != SCI_OK) return st;
@@ -1078,10 +1080,9 @@ int sci_gap_tv_adaptive(sci_ctx *ctx, sci_dims d, const sci_solver_params *p, co
     float *pred = (float *)ctx->ws[WS_XTMP].ptr;
     const sci_tv_params &q = t0;
     if ((st = ensure_ws(ctx, WS_CBITS, cbits_bytes(d), stream)) != SCI_OK) return st;
-    launch_weights(d.nx, d.ny, d.B, C, 0.0f, Sinv, stream);
-    launch_pack_masks(d.nx, d.ny, d.B, C, cbits_ptr(ctx), cflag_ptr(ctx, d), stream);
+    launch_setup(d.nx, d.ny, d.B, C, Y, 0.0f, Sinv, X_init ? nullptr : theta, nullptr, cbits_ptr(ctx),
+                 cflags_ptr(ctx, d), stream);
     if (X_init) launch_copy(X_init, theta, vb, stream);
-    else launch_adjoint(d.nx, d.ny, d.B, C, Y, theta, stream);
     if (p->outer_iters == 0) launch_copy(theta, X_out, vb, stream);
     if ((st = check_launch(ctx, "adaptive setup")) != SCI_OK) return st;
     FgpRun r;
@@ -1089,7 +1090,7 @@ int sci_gap_tv_adaptive(sci_ctx *ctx, sci_dims d, const sci_solver_params *p, co
     int inner = 0, fallbacks = 0, net_starts = 0;
     const void *keep = nullptr;
     for (int t = 0; t < p->outer_iters; ++t) {
-        launch_gap_project(d.nx, d.ny, d.B, theta, C, Y, Sinv, X_out, stream, cbits_ptr(ctx), cflag_ptr(ctx, d));
+        launch_gap_project(d.nx, d.ny, d.B, theta, C, Y, Sinv, X_out, stream, cbits_ptr(ctx), cflags_ptr(ctx, d));
         if ((st = check_launch(ctx, "k_project")) != SCI_OK) return st;
         const void *init = nullptr;
         // a correcting network (3 input channels) needs the previous call's final dual,
