@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <array>
 #include <map>
 #include <string>
 #include <vector>
@@ -74,6 +75,14 @@ struct sci_ctx {
     std::vector<sci::ProfRec> prof;
     // fused-schedule tile shape chosen by the autotuner, per problem key
     std::map<std::string, std::pair<int, int>> tuned; // (tile shape, number of passes)
+    // the last choices of the fused schedule (pick_tiling), by sizes and options
+    // alone: a solve asks for the same one on every outer iteration
+    struct Pick {
+        std::array<int32_t, 13> key;
+        int shape = 0, npass = 0; // npass 0: unused entry
+    };
+    std::array<Pick, 4> picks;
+    unsigned next_pick = 0;
 };
 
 namespace sci {
