@@ -266,7 +266,9 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
             float thn[2][KF], qh[2][KF], qv[2][KF], n2[2] = {0.0f, 0.0f};
             auto pre = [&](int sidx, int t) {
                 const int r = k0 + sidx - t;
-                const float step_v = row_step(r, nx, step);
+                // uniform per row; the scalar form pays in the projection step only
+                // (Chambolle-2004, 740x1041x13: 205 us with it, 196 with the select)
+                const float step_v = CH_STEP ? ((r >= 0 && r < nx - 1) ? step : 0.0f) : row_step(r, nx, step);
 #pragma unroll
                 for (int kk = 0; kk < KF; ++kk) {
                     thn[sidx][kk] = theta_of(xl[t + 1 - sidx][kk], from_left(ih[sidx][kk]), ih[sidx][kk], cwv[t][kk],
