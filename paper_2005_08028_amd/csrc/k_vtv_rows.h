@@ -103,6 +103,12 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
     static_assert(QIO == 0 || !CH_STEP, "dual records: projection passes");
     static_assert(!QIN || MODE >= 1, "a record input needs a dual start");
     constexpr int CH = kRowChunk;
+    // Scheduling stops at a change of priority, which costs registers: with two
+    // frames, 16-bit duals and the Chambolle-2004 step, passes of 6 cross 128, a
+    // SIMD no longer takes four wavefronts and a CU often only one 5-wavefront
+    // workgroup (bf16, cold pass of 6 at 164x159x10: 21 us without, 29 with;
+    // Chambolle-2004, 11 iterations at 953x1334x10: 292 and 343 us).
+    constexpr bool PRIO = KF >= 3 || (DT == DT_F32 && (!CH_STEP || KF == 1 || M <= 5));
     constexpr int TXO = 64 - 2 * M - 1; // interior columns per strip
     static_assert(TXO > 0, "strip too narrow for the pass length");
     static_assert(CH == 2, "steps run in pairs, one pair per chunk");
@@ -312,12 +318,12 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
             };
             // a wavefront on its way to the barrier goes before one that has
             // passed it: the barrier waits for the last
-            __builtin_amdgcn_s_setprio(2);
+            if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
             if (runA) pre(0, tau);
             if (runB) pre(1, tau - 1);
             n2s[par][g][lane] = make_float2(n2[0], n2[1]);
             lds_barrier();
-            __builtin_amdgcn_s_setprio(0);
+            if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
             float totA = 0.0f, totB = 0.0f;
 #pragma unroll
             for (int gg = 0; gg < NS; ++gg) {
