@@ -108,7 +108,8 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
     // SIMD no longer takes four wavefronts and a CU often only one 5-wavefront
     // workgroup (bf16, cold pass of 6 at 164x159x10: 21 us without, 29 with;
     // Chambolle-2004, 11 iterations at 953x1334x10: 292 and 343 us).
-    constexpr bool PRIO = KF >= 3 || (DT == DT_F32 && (!CH_STEP || KF == 1 || M <= 5));
+    // With eight exchange slots so does the float32 warm pass of 5 (126 to 135).
+    constexpr bool PRIO = KF >= 3 || (DT == DT_F32 && (KF == 1 || (CH_STEP ? M <= 5 : M != 5 || MODE != 1 || NS == 5)));
     constexpr int TXO = 64 - 2 * M - 1; // interior columns per strip
     static_assert(TXO > 0, "strip too narrow for the pass length");
     static_assert(CH == 2, "steps run in pairs, one pair per chunk");
