@@ -81,10 +81,10 @@ __device__ inline float from_right(float v) { return __builtin_amdgcn_update_dpp
 __device__ inline float proj_atv(float q) { return __builtin_amdgcn_fmed3f(q, -1.0f, 1.0f); }
 
 // Isotropic scale 1 / max(1, sqrt(n2)) = min(1, 1/sqrt(n2)) for a squared norm
-// n2 >= 0. The median with 0 and 1 becomes the output clamp of v_rsq_f32 and
-// costs no instruction (fminf is one of the 18 of an ITV2D voxel-iteration).
-// A NaN norm gives 0.
-__device__ inline float iso_scale(float n2) { return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rsqf(n2), 0.0f, 1.0f); }
+// n2 >= 0. A NaN norm gives 1 (fminf returns its other operand): the finite
+// components of that pixel, with VTV the other frames', stay as they are. The
+// median with 0 and 1 would be the free output clamp of v_rsq_f32 but gives 0.
+__device__ inline float iso_scale(float n2) { return fminf(1.0f, __builtin_amdgcn_rsqf(n2)); }
 
 // Semi-implicit (Chambolle 2004) scale 1 / (1 + sqrt(n2)) for the squared
 // norm n2 of z/(8 lambda), with the hardware square root and reciprocal

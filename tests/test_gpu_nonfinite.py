@@ -1,0 +1,44 @@
+"""A pixel that is NaN or infinite reaches the same outputs as in the oracle:
+the isotropic projection divides by max(1, norm), which is 1 for a NaN norm, so
+the finite components of such a pixel (with VTV the other frames) keep their
+values. The pixel lies further from the edges than the iterations reach."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import oracle as orc  # noqa: E402
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("tv,B", [("itv2d", 2), ("vtv", 3), ("vtv", 9), ("vtv", 11), ("vtv", 17), ("vtv", 25)])
+def test_nonfinite_pixel(tv, B, warm, bad):
+    from paper_2005_08028_amd import scitv
+
+    nx, ny, n = 40, 150, 3
+    rng = np.random.default_rng(B)
+    X = rng.random((B, nx, ny)).astype(np.float32)
+    X[B // 2, 20, 75] = bad
+    P = (0.3 * rng.standard_normal((2, B, nx, ny))).astype(np.float32) if warm else None
+    if warm:
+        P[0, :, :, -1] = 0.0
+        P[1, :, -1, :] = 0.0
+    lam = float(np.float32(0.07))
+    want = orc.tv_denoise(X, lam, n, tv=tv, p_init=P, return_dual=True)
+    ctx = scitv.Context(0)
+    shapes = range(1, scitv.sci_tile_shape_count() + 1) if tv == "itv2d" else (0,)
+    for kw in [dict(schedule="stream")] + [dict(schedule="fused", tile_shape=s) for s in shapes]:
+        prm = scitv.tv_params(tv=tv, lam=lam, n_inner=n, **kw)
+        D = torch.empty((2, B, nx, ny), device="cuda")
+        th, _, _, _ = scitv.sci_tv_denoise(ctx.handle, torch.from_numpy(X).cuda(), prm,
+                                           dual_init=torch.from_numpy(P).cuda() if warm else None, dual_out=D)
+        for got, ref in ((th, want[0]), (D, want[1])):
+            got = got.double().cpu().numpy()
+            np.testing.assert_array_equal(np.isnan(got), np.isnan(ref), err_msg=str(kw))
+            # float32 rounding through 3 iterations of step 1 / (8 lam) < 2: a few
+            # ulp of values below 4, times the growth of the extrapolation
+            ok = np.isfinite(ref)
+            np.testing.assert_allclose(got[ok], ref[ok], rtol=0, atol=2e-5, err_msg=str(kw))
+    ctx.close()
