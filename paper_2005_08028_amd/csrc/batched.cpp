@@ -305,10 +305,10 @@ int sci_gap_tv_batched(sci_ctx *ctx, int32_t n, const sci_problem *probs, const 
         return enqueue_batch(ctx, pl, tab, *p, stream);
     }
     // graph: keyed by every pointer and size of the batch; owns its own table
-    std::string key = "batched|" + batch_key(*p, n, probs) + "|" + std::to_string(pl.shape[0]) + "|" + std::to_string(pl.shape[1]) + "|" +
-                      std::to_string(p->outer_iters) + "|" + std::to_string(p->tv.lambda) + "|" +
-                      std::to_string(p->tv.accel);
-    char buf[64];
+    char buf[128];
+    snprintf(buf, sizeof buf, "|%d,%d|%d|%.9g|%d", pl.shape[0], pl.shape[1], p->outer_iters, (double)p->tv.lambda,
+             p->tv.accel); // nine digits tell every two floats apart
+    std::string key = "batched|" + batch_key(*p, n, probs) + buf;
     for (int k = 0; k < pl.n; ++k) {
         const BatchProb &b = pl.tab[k];
         snprintf(buf, sizeof buf, "|%p,%p,%p,%p,%d", (const void *)b.Y, (const void *)b.C, (void *)b.x,
