@@ -239,7 +239,10 @@ double call_us(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, in
 // are rounded between passes, so their split is fixed: one pass for a cold
 // call of at most kTileMaxM iterations whose dual is not kept when the
 // row-pipelined shapes fill the chip, else passes of about kDefaultPassLen;
-// passes that touch a 16-bit dual run shape 0 whatever is chosen.
+// passes that touch a 16-bit dual run shape 0 whatever is chosen. A chunk of a
+// gap-controlled call (cd.more) runs in the fewest passes but where both the
+// split and the shape are free: an explicit or tuned count is that of a whole
+// fixed-count call.
 //
 // Weighing up to 48 pairs takes over 1 us of host time, a tenth of a small
 // outer iteration (FISTA-ATV 80x59x1, 40 x 3: 409 us, with the last choices
@@ -258,14 +261,16 @@ void pick_tiling(sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, int n,
     const int min_pass = (n + kTileMaxM - 1) / kTileMaxM;
     const bool cold = !cd.in && !cd.out;
     *shape = 0;
-    *npass = (n + kDefaultPassLen - 1) / kDefaultPassLen;
+    *npass = cd.more ? min_pass : (n + kDefaultPassLen - 1) / kDefaultPassLen;
     auto it = ctx->tuned.find(tune_key(p, d));
     if (it != ctx->tuned.end()) {
         *shape = it->second.first;
-        *npass = it->second.second;
+        if (!cd.more) *npass = it->second.second;
     } else if (tile_supported(p.tv) && !p.chambolle04 && n >= 1) {
         int lo = min_pass, hi = std::min(n, min_pass + 2);
-        if (p.tile_passes >= 1) {
+        if (cd.more) {
+            if (p.dual_dtype != SCI_DUAL_F32 || p.tile_shape >= 1 || p.tile_passes >= 1) hi = lo;
+        } else if (p.tile_passes >= 1) {
             lo = hi = std::min(n, std::max(min_pass, p.tile_passes));
         } else if (p.dual_dtype != SCI_DUAL_F32) {
             lo = hi = cold && n <= kTileMaxM && default_row_shape(ctx, d, n) >= 0 ? 1 : std::max(min_pass, *npass);
@@ -292,7 +297,7 @@ void pick_tiling(sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, int n,
         }
     }
     if (p.tile_shape >= 1) *shape = p.tile_shape - 1;
-    if (p.tile_passes >= 1) *npass = p.tile_passes;
+    if (p.tile_passes >= 1 && !cd.more) *npass = p.tile_passes;
     if (*npass < min_pass) *npass = min_pass;
     if (*npass > n) *npass = n;
     ctx->picks[ctx->next_pick++ % ctx->picks.size()] = {key, *shape, *npass};
@@ -844,10 +849,7 @@ int fgp_chunk(sci_ctx *ctx, const sci_dims &d, const sci_tv_params &q, const flo
 {
     const bool fused = q.schedule != SCI_SCHED_STREAM && fused_supported(q, d);
     if (q.schedule == SCI_SCHED_FUSED && !fused) return fail(ctx, SCI_ERR_UNSUPPORTED, kFusedScope);
-    // the fewest passes with 16-bit duals, whose rounding depends on the split
-    if (fused)
-        return fgp_tile_iterate(ctx, d, q, x, r, n, nullptr, nullptr, true, s, -1,
-                                q.dual_dtype != SCI_DUAL_F32 ? (n + kTileMaxM - 1) / kTileMaxM : -1, true);
+    if (fused) return fgp_tile_iterate(ctx, d, q, x, r, n, nullptr, nullptr, true, s, -1, -1, true);
     return fgp_iterate(ctx, d, q, x, r, n, s);
 }
 

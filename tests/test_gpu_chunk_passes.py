@@ -1,0 +1,44 @@
+"""Passes of a gap-controlled call: each check interval runs in the fewest
+on-chip passes where nothing is gained by more (the Chambolle-2004 step, a tuned
+or explicit pass count, which are for the whole fixed-count call), counted
+through the profiler."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _launches(scitv, ctx, X, **kw):
+    prm = scitv.tv_params(tv=kw.pop("tv"), lam=0.07, gap_tol=1e-30, **kw)
+    scitv.sci_tv_denoise(ctx.handle, X, prm)
+    scitv.sci_profile_enable(ctx.handle, True)
+    _, _, its, _ = scitv.sci_tv_denoise(ctx.handle, X, prm)
+    n, _ = scitv.sci_profile_read(ctx.handle, "fgp_fused")
+    scitv.sci_profile_enable(ctx.handle, False)
+    assert its == kw["n_inner_max"]
+    return n
+
+
+@pytest.mark.parametrize("tv", ["atv", "itv2d"])
+@pytest.mark.parametrize("every,most,passes", [(0, 20, 2), (7, 20, 3), (15, 30, 4)])
+def test_chambolle04(tv, every, most, passes):
+    from paper_2005_08028_amd import scitv
+
+    X = torch.rand((3, 60, 140), device="cuda")
+    ctx = scitv.Context(0)
+    kw = dict(tv=tv, n_inner=5, n_inner_max=most, gap_check_every=every, chambolle04=True, accel=False)
+    assert _launches(scitv, ctx, X, **kw) == passes
+    ctx.close()
+
+
+@pytest.mark.parametrize("tv", ["atv", "itv2d"])
+def test_explicit_and_tuned_pass_counts(tv):
+    from paper_2005_08028_amd import scitv
+
+    X = torch.rand((3, 60, 140), device="cuda")
+    ctx = scitv.Context(0)
+    kw = dict(tv=tv, n_inner=30, n_inner_max=30, gap_check_every=10)
+    assert _launches(scitv, ctx, X, tile_passes=5, **kw) == 3
+    scitv.sci_autotune(ctx.handle, X, scitv.tv_params(tv=tv, lam=0.07, n_inner=30))
+    assert _launches(scitv, ctx, X, **kw) == 3
+    ctx.close()
