@@ -42,3 +42,16 @@ def test_explicit_and_tuned_pass_counts(tv):
     scitv.sci_autotune(ctx.handle, X, scitv.tv_params(tv=tv, lam=0.07, n_inner=30))
     assert _launches(scitv, ctx, X, **kw) == 3
     ctx.close()
+
+
+# sizes where the fewest passes of the 64 x 64 tile measured 7 to 10 % faster than
+# the split with the smallest estimate, which is less than a fifth smaller
+@pytest.mark.parametrize("tv,B,nx,ny,every,passes", [("itv2d", 10, 172, 216, 15, 2), ("itv2d", 20, 139, 146, 15, 2),
+                                                     ("atv", 8, 855, 259, 20, 2), ("itv2d", 27, 589, 334, 10, 1)])
+def test_untuned(tv, B, nx, ny, every, passes):
+    from paper_2005_08028_amd import scitv
+
+    X = torch.rand((B, nx, ny), device="cuda")
+    ctx = scitv.Context(0)
+    assert _launches(scitv, ctx, X, tv=tv, n_inner=5, n_inner_max=2 * every, gap_check_every=every) == 2 * passes
+    ctx.close()
