@@ -43,8 +43,10 @@ int launch_fgp_tile(int tv, int dual_dtype, int m, int shape, int nx, int ny, in
 {
     if (m < 1 || m > kTileMaxM || shape < 0 || shape >= tile_shape_count()) return SCI_ERR_INVALID_ARG;
     // A cold pass that neither returns nor keeps the dual never stores it, so
-    // its storage type does not matter: 16-bit requests take the float32 row
-    // kernels too (same bits as a float32 pass; registers are float32).
+    // its storage type does not matter: 16-bit requests take the float32
+    // kernels and the shape asked for (same bits as a float32 pass; registers
+    // are float32). ITV2D, 5 iterations at 640x480x4 in bf16: 12.1 us in the 16-bit
+    // tile, 9.9 like this (float32: 9.9).
     const bool no_dual_io = tp.mode == 0 && !tp.pn_out && !tp.pp_out;
     if (tv == TV_VTV) // one row-pipelined kernel, whatever the shape
         return launch_vtv_rows(m, nx, ny, B, x, tp, lam, s, chambolle04, no_dual_io ? DT_F32 : dual_dtype);
@@ -55,7 +57,8 @@ int launch_fgp_tile(int tv, int dual_dtype, int m, int shape, int nx, int ny, in
         return launch_rows_ch_f32(tv, H, m, nx, ny, B, x, tp, lam, s);
     }
     if (!tile_supported(tv)) return SCI_ERR_UNSUPPORTED;
-    if ((dual_dtype == DT_F32 || no_dual_io) && tile_shape_pipelined(shape)) {
+    if (no_dual_io) dual_dtype = DT_F32;
+    if (dual_dtype == DT_F32 && tile_shape_pipelined(shape)) {
         int H = 0, w = 0, c = 0;
         tile_shape_info(shape, &H, &w, &c);
         return tv == TV_ATV ? launch_rows_atv_f32(H, m, nx, ny, B, x, tp, lam, s)
