@@ -88,39 +88,43 @@ int validate(sci_ctx *ctx, int n, const sci_problem *probs, const sci_solver_par
 // (each choice gives the same bits). 12 measurements of 256^2 to 1024^2, 5 ATV
 // iterations: 102 us per launch over all of them and 15 us over the last with
 // shape 1 (the earlier default), 68 and 15 us with the pair; one
-// row-pipelined shape for both 68 and 38 us.
+// row-pipelined shape for both 68 and 38 us. Only the active counts that are
+// launched are weighed, and equal neighbours share their tile counts: this runs
+// on the host before every call (512 measurements of about 70x75x4, one
+// iteration: 219 us a call with every count weighed, 117 us like this).
 void choose_shapes(const sci_ctx *ctx, const sci_problem *probs, const sci_solver_params &p, const std::vector<int> &T,
                    BatchPlan &pl)
 {
     const int n = pl.n, ns = tile_shape_count();
-    std::vector<double> cost((size_t)ns * (n + 1), 0.0); // of one launch over the first k problems
+    std::vector<int> counts; // active problems of a launch
+    std::vector<double> launches;
+    for (int k = 1; k <= n; ++k) {
+        const int t = T[k - 1] - (k < n ? T[k] : 0);
+        if (t == 0) continue;
+        counts.push_back(k);
+        launches.push_back(t);
+    }
+    const int nc = (int)counts.size();
+    if (nc == 0) return; // no iterations
+    std::vector<double> cost((size_t)ns * nc); // of one launch, per shape and count
     for (int sh = 0; sh < ns; ++sh) {
-        long units = 0;
+        long units = 0, frame = 0;
         double voxels = 0.0;
+        int c = 0;
         for (int k = 0; k < n; ++k) {
             const sci_dims &d = probs[pl.order[k]].d;
-            units += tile_units(sh, pl.m, d.nx, d.ny) * d.B;
+            const bool same = k > 0 && d.nx == probs[pl.order[k - 1]].d.nx && d.ny == probs[pl.order[k - 1]].d.ny;
+            if (!same) frame = tile_units(sh, pl.m, d.nx, d.ny);
+            units += frame * d.B;
             voxels += (double)d.nx * d.ny * d.B;
-            cost[(size_t)sh * (n + 1) + k + 1] = tile_pass_us(ctx->num_cus, p.tv.tv, sh, pl.m, units, voxels, 2);
+            if (k + 1 < counts[c]) continue;
+            cost[(size_t)sh * nc + c++] = tile_pass_us(ctx->num_cus, p.tv.tv, sh, pl.m, units, voxels, 2);
+            if (c == nc) break;
         }
     }
-    auto launches = [&](int k) { return (double)(T[k - 1] - (k < n ? T[k] : 0)); }; // over the first k problems
-    double best = -1.0;
-    for (int a = 0; a < ns; ++a)
-        for (int b = a; b < ns; ++b) {
-            double t = 0.0;
-            for (int k = 1; k <= n; ++k)
-                t += launches(k) * std::min(cost[(size_t)a * (n + 1) + k], cost[(size_t)b * (n + 1) + k]);
-            if (best < 0.0 || t < best) {
-                best = t;
-                pl.shape[0] = a;
-                pl.shape[1] = b;
-            }
-        }
-    pl.ntab = pl.shape[0] == pl.shape[1] ? 1 : 2;
-    for (int k = 1; k <= n; ++k)
-        pl.use[k] = pl.ntab == 2 &&
-                    cost[(size_t)pl.shape[1] * (n + 1) + k] < cost[(size_t)pl.shape[0] * (n + 1) + k];
+    pl.ntab = pick_shape_pair(ns, nc, cost.data(), launches.data(), pl.shape);
+    for (int c = 0; c < nc; ++c)
+        pl.use[counts[c]] = pl.ntab == 2 && cost[(size_t)pl.shape[1] * nc + c] < cost[(size_t)pl.shape[0] * nc + c];
 }
 
 void plan_batch(const sci_ctx *ctx, int n, const sci_problem *probs, const sci_solver_params &p, int shape_override,

@@ -217,6 +217,7 @@ bool tile_shape_pipelined(int shape);
 // Cost model of the fused 2D passes (tile_model.cpp).
 long tile_units(int shape, int m, int nx, int ny);
 double tile_pass_us(int num_cus, int tv, int shape, int m, long units, double voxels, int io);
+int pick_shape_pair(int ns, int nc, const double *cost, const double *launches, int shape[2]);
 // Row-pipelined VTV passes: the longest pass for B frames (0 when the kernel
 // does not run them), and one pass of m iterations with the duals read and
 // written between passes in dual_dtype (16-bit: projection step only).

@@ -93,4 +93,25 @@ double tile_pass_us(int num_cus, int tv, int shape, int m, long units, double vo
     return std::max(cyc / kClockPerUs + kLaunchUs, bytes / (bytes < 2.2e8 ? 7.5e6 : io > 4 ? 3.2e6 : 5.0e6) + 2.0);
 }
 
+// The shape, or the two shapes of which every launch takes the cheaper, with the
+// smallest total of launches[c] * cost[shape * nc + c]. Returns their number: 2
+// only where the second one lowers the total of the best single shape.
+int pick_shape_pair(int ns, int nc, const double *cost, const double *launches, int shape[2])
+{
+    double best = -1.0;
+    int found = 0;
+    for (int gap = 0; gap < ns; ++gap) // single shapes first
+        for (int a = 0; a + gap < ns; ++a) {
+            const double *ca = cost + (size_t)a * nc, *cb = cost + (size_t)(a + gap) * nc;
+            double t = 0.0;
+            for (int c = 0; c < nc; ++c) t += launches[c] * std::min(ca[c], cb[c]);
+            if (best >= 0.0 && t >= best) continue;
+            best = t;
+            shape[0] = a;
+            shape[1] = a + gap;
+            found = gap ? 2 : 1;
+        }
+    return found;
+}
+
 } // namespace sci
