@@ -1,6 +1,9 @@
 // Tile shapes of the fused-schedule kernel, as (rows per wavefront R,
 // wavefronts per workgroup NW, columns per lane C, occupancy hint WPE).
-// Tile = (64*C) x (NW*R) pixels including the recomputed halo.
+// Tile = (64*C) x (NW*R) pixels including the recomputed halo. The 64 x 80 tile
+// needs its hint of 8 for two workgroups per CU (64 registers): with 4, passes of
+// 8 to 10 take 66 (10 iterations at 1024x1024x8: ATV 109 us, with 8 75; ITV2D 137
+// and 100).
 #pragma once
 
 #define SCI_TILE_SHAPES(X)                                                                                          \
@@ -13,7 +16,7 @@
     X(6, 7, 16, 2, 4) /* 128 x 112, 1024 threads */                                                                 \
     X(7, 6, 16, 2, 4) /* 128 x 96,  1024 threads */                                                                 \
     X(8, 6, 12, 3, 3) /* 192 x 72,  768 threads  */                                                                 \
-    X(15, 5, 16, 1, 4) /* 64 x 80,  1024 threads */
+    X(15, 5, 16, 1, 8) /* 64 x 80,  1024 threads */
 
 // Row-pipelined shapes (k_fgp_rows.h), numbered after the first nine tiled ones
 // (shapes added later keep the numbers callers know): one wavefront walks a
