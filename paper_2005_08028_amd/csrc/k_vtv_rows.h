@@ -88,6 +88,45 @@ template <int DT> __device__ inline uint32_t vtv_pack16(float a, float b)
     else return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, vtv_h2));
 }
 
+// Three forms of the same step. Full: priorities around the exchange, the
+// scalar row step, empty frame slots zeroed on load; they save instructions and
+// waiting but hold values longer (scheduling stops at a change of priority).
+// Quiet: no priorities. Lean: none of the three.
+enum class VtvForm { kFull, kQuiet, kLean };
+
+// The form of a kernel, by its registers. Four wavefronts per SIMD (at most 128)
+// hold the two workgroups per CU that the segment height counts on; with three
+// (at most 168) two of 5 or 6 wavefronts count as resident but run one after
+// the other, two of 7 or 8 do not count. 512x512, microseconds in the full
+// or quiet form -> in the form chosen: warm 5 of B = 9 in bf16 (136 -> 128
+// registers) 49.5 -> 31.2, of B = 16 43.7 -> 39.2; warm Chambolle-2004 5 of B = 9
+// (133 -> 127) 48.0 -> 33.7; cold 2 of B = 25 (130 -> 126) 24.6 -> 22.7. Registers
+// grow with M + MODE by about 6.5 per frame, so with two frames 128 lies at 6,
+// with four at 2; there the kernels that cross it take the richest form that
+// does not. The 168 line needs no such care: below it 5 or 6 wavefronts run one
+// workgroup at a time on segments cut for two (warm 8 of B = 9: 84 us at 168
+// registers, 60 at 170).
+constexpr VtvForm vtv_form(int m, int kf, int mode, int ch_step, int dt, int qio, int ns)
+{
+    if (kf == 1) {
+        // Measured over seven sizes from 68x107x3 to 512x512x8: with float32 duals
+        // the full form is the faster one (cold 5 at 985x56x3 11.2 us, lean 12.0)
+        // but for cold passes of 7 (68x107x3 11.1, lean 10.0; 985x56x3 16.3 and
+        // 15.4); with 16-bit duals the lean one (warm 10, quiet 1 to 6 % longer).
+        return dt != DT_F32 || (m == 7 && mode == 0 && !ch_step) ? VtvForm::kLean : VtvForm::kFull;
+    }
+    if (kf == 2 && ns == kVtvMaxWaves) {
+        if (m == 4 && mode == 2 && dt == DT_F32 && (ch_step || qio >= 2)) return VtvForm::kLean;
+        if (m == 5 && mode == 1 && (ch_step || (dt != DT_F32 && qio < 2))) return VtvForm::kLean;
+        if (m == 5 && mode == 2 && dt != DT_F32 && qio == 3) return VtvForm::kLean;
+        // the priorities alone cross 128 with 16-bit duals, the Chambolle-2004
+        // step beyond 5 iterations and warm passes of 5
+        if (dt != DT_F32 || (ch_step && m > 5) || (m == 5 && mode == 1)) return VtvForm::kQuiet;
+    }
+    if (kf == 4 && m == 2 && mode == 0 && dt == DT_F32 && !ch_step) return VtvForm::kQuiet;
+    return VtvForm::kFull;
+}
+
 template <int M, int KF, int MODE, int CH_STEP, int DT, int QIO, int NS>
 __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int fpw, int nstrip, int H,
                                                               const float *__restrict__ x,
@@ -103,13 +142,8 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
     static_assert(QIO == 0 || !CH_STEP, "dual records: projection passes");
     static_assert(!QIN || MODE >= 1, "a record input needs a dual start");
     constexpr int CH = kRowChunk;
-    // Scheduling stops at a change of priority, which costs registers: with two
-    // frames, 16-bit duals and the Chambolle-2004 step, passes of 6 cross 128, a
-    // SIMD no longer takes four wavefronts and a CU often only one 5-wavefront
-    // workgroup (bf16, cold pass of 6 at 164x159x10: 21 us without, 29 with;
-    // Chambolle-2004, 11 iterations at 953x1334x10: 292 and 343 us).
-    // With eight exchange slots so does the float32 warm pass of 5 (126 to 135).
-    constexpr bool PRIO = KF >= 3 || (DT == DT_F32 && (KF == 1 || (CH_STEP ? M <= 5 : M != 5 || MODE != 1 || NS == 5)));
+    constexpr VtvForm FORM = vtv_form(M, KF, MODE, CH_STEP, DT, QIO, NS);
+    constexpr bool PRIO = FORM == VtvForm::kFull, LEAN = FORM == VtvForm::kLean;
     constexpr int TXO = 64 - 2 * M - 1; // interior columns per strip
     static_assert(TXO > 0, "strip too narrow for the pass length");
     static_assert(CH == 2, "steps run in pairs, one pair per chunk");
@@ -154,7 +188,7 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
 #pragma unroll
     for (int kk = 0; kk < KF; ++kk) cpm[kk] = 0.0f;
     int par = 0; // LDS buffer of the next exchange
-    // Every exchange reads all kVtvMaxWaves slots (one fixed run of LDS reads,
+    // Every exchange reads all NS slots (one fixed run of LDS reads,
     // no loop over ng); the slots of absent wavefronts hold +0, which leaves
     // the non-negative sum unchanged. The first exchange's barrier orders
     // these writes before any read.
@@ -216,8 +250,8 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
 #pragma unroll
             for (int kk = 0; kk < KF; ++kk) {
                 // a slot past the last frame holds x = p = 0 and adds nothing
-                // to the norm
-                const bool real = kk < nk;
+                // to the norm (lean form: its norm is left out instead)
+                const bool real = LEAN || kk < nk;
                 const bool hin = iin && hj && real;                   // horizontal difference exists
                 const bool vin = i >= 0 && i < nx - 1 && jin && real; // vertical difference exists
                 x0[s][kk] = (iin && jin && real) ? xn[s][kk] : 0.0f;
@@ -275,23 +309,26 @@ __global__ __launch_bounds__(64 * NS) void k_vtv_rows(int nx, int ny, int B, int
                 const int r = k0 + sidx - t;
                 // uniform per row; the scalar form pays in the projection step only
                 // (Chambolle-2004, 740x1041x13: 205 us with it, 196 with the select)
-                const float step_v = CH_STEP ? ((r >= 0 && r < nx - 1) ? step : 0.0f) : row_step(r, nx, step);
+                const float step_v =
+                    CH_STEP || LEAN ? ((r >= 0 && r < nx - 1) ? step : 0.0f) : row_step(r, nx, step);
 #pragma unroll
                 for (int kk = 0; kk < KF; ++kk) {
                     thn[sidx][kk] = theta_of(xl[t + 1 - sidx][kk], from_left(ih[sidx][kk]), ih[sidx][kk], cwv[t][kk],
                                              iv[sidx][kk], lam);
                     const float zh = from_right(cth[t][kk]) - cth[t][kk];
                     const float zv = thn[sidx][kk] - cth[t][kk];
+                    float n2a;
                     if (CH_STEP) {
                         const float sh = step_h * zh, sv = step_v * zv;
                         qh[sidx][kk] = cwh[t][kk] + sh;
                         qv[sidx][kk] = cwv[t][kk] + sv;
-                        n2[sidx] = norm2_add(n2[sidx], sh, sv);
+                        n2a = norm2_add(n2[sidx], sh, sv);
                     } else {
                         qh[sidx][kk] = ascend(cwh[t][kk], zh, step_h);
                         qv[sidx][kk] = ascend(cwv[t][kk], zv, step_v);
-                        n2[sidx] = norm2_add(n2[sidx], qh[sidx][kk], qv[sidx][kk]);
+                        n2a = norm2_add(n2[sidx], qh[sidx][kk], qv[sidx][kk]);
                     }
+                    n2[sidx] = !LEAN || kk < nk ? n2a : n2[sidx];
                 }
             };
             auto post = [&](int sidx, int t, float tot) {

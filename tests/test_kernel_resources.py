@@ -65,3 +65,21 @@ def test_tall_tile_runs_two_workgroups(kernels):
     # 16 wavefronts of 5 rows a lane: the cost model counts two of them per CU
     tiles = {t: v for t, v in _templates(kernels, "k_fgp_tile").items() if t[3:6] == (5, 16, 1)}
     assert len(tiles) == 20 and max(tiles.values()) <= 64
+
+
+# (M, frames, mode, Chambolle-2004, dual type, records) beyond the rule below: these
+# cross 128 registers in every form ...
+OVER = {(2, 4, 0, 1, 0, 0), (4, 2, 2, 0, 0, 0), (4, 2, 2, 0, 0, 1), (4, 2, 2, 0, 1, 0), (4, 2, 2, 0, 1, 2),
+        (4, 2, 2, 0, 2, 0), (4, 2, 2, 0, 2, 2), (5, 2, 1, 0, 0, 0), (5, 2, 1, 0, 0, 1), (5, 2, 1, 0, 2, 0),
+        (6, 2, 0, 0, 0, 0), (6, 2, 0, 0, 0, 2), (6, 2, 0, 0, 1, 0), (6, 2, 0, 0, 2, 0)}
+# ... and these do not
+UNDER = {(5, 2, 2, 0, 1, 3), (5, 2, 2, 0, 2, 3)}
+
+
+def test_vtv_passes_hold_two_workgroups(kernels):
+    short = {2: 6, 3: 3, 4: 2}  # largest M + mode at 128 registers, by frames per wavefront
+    missed = {t: v for t, v in _templates(kernels, "k_vtv_rows").items()
+              if t[1] > 1 and v > 128 and (t[0] + t[2] <= short[t[1]] and t[:6] not in OVER or t[:6] in UNDER)}
+    # five slots serve five wavefronts, of which two workgroups fit at 168 too
+    assert not {t: v for t, v in missed.items() if t[6] == 8}
+    assert all(v <= 168 for v in missed.values())
