@@ -195,7 +195,10 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     constexpr int NPRO = (2 * (M - 1) + CH - 1) / CH;
     // The rows loaded during a chunk go to the ring (and are waited for) at its
     // end, before its last stores: a wait further on would wait for those
-    // stores too, which vmcnt counts with the loads.
+    // stores too, which vmcnt counts with the loads. (Not the duals of a warm
+    // momentum pass of 10: held that much longer, ATV needs two to four of its
+    // 256 registers more and spills.)
+    constexpr bool SETTLE = MODE < 2 || M < kTileMaxM;
     auto settle_chunk = [&](int i0) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -203,11 +206,11 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
             const int slot = (((i0 + s) % P) + P) % P;
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                if (MODE >= 1) {
+                if (MODE >= 1 && SETTLE) {
                     settle(lh[s][c]);
                     settle(lv[s][c]);
                 }
-                if (MODE == 2) {
+                if (MODE == 2 && SETTLE) {
                     settle(mh[s][c]);
                     settle(mv[s][c]);
                 }

@@ -1,6 +1,7 @@
-"""Registers of the compiled kernels, read from the metadata in the library (no
-GPU needed): the kernels whose launches count on two workgroups per CU have the
-registers for it (a SIMD holds 512: 8 wavefronts at 64, 4 at 128, 3 at 168)."""
+"""Registers and scratch of the compiled kernels, read from the metadata in the
+library (no GPU needed): nothing spills, and the kernels whose launches count on
+two workgroups per CU have the registers for it (a SIMD holds 512: 8 wavefronts
+at 64, 4 at 128, 3 at 168)."""
 import os
 import re
 import struct
@@ -59,6 +60,10 @@ def _templates(kernels, name):
             out[tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(1)))] = k[".vgpr_count"]
     assert out
     return out
+
+
+def test_no_scratch(kernels):
+    assert not [n for n, k in kernels.items() if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
 
 
 def test_tall_tile_runs_two_workgroups(kernels):
