@@ -193,6 +193,12 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     const int nsteps = H + 2 * M + 1;
     const int nchunk = (nsteps + CH - 1) / CH; // >= M + 1 > NPRO
     constexpr int NPRO = (2 * (M - 1) + CH - 1) / CH;
+    // Cold ITV2D passes take the scale without a NaN case up to the first chunk
+    // that has a pixel beyond the limit. 1024x1024x24, 10 iterations: 176.8 us
+    // with iso_scale throughout, 167.4 like this; 5 iterations 82.3 and 79.0.
+    constexpr bool TAME = MODE == 0 && TV != TV_ATV && !CH_STEP;
+    const float limit = no_nan_limit(lam);
+    uint64_t tame = ~0ull; // lanes, ANDed as masks: no branch
     // The rows loaded during a chunk go to the ring (and are waited for) at its
     // end, before its last stores: a wait further on would wait for those
     // stores too, which vmcnt counts with the loads. (Not the duals of a warm
@@ -201,6 +207,12 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     constexpr bool SETTLE = MODE < 2 || M < kTileMaxM;
     auto settle_chunk = [&](int i0) {
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TAME) {
+#pragma unroll
+            for (int s = 0; s < CH; ++s)
+#pragma unroll
+                for (int c = 0; c < C; ++c) tame &= __ballot(fabsf(xn[s][c]) <= limit);
+        }
 #pragma unroll
         for (int s = 0; s < CH; ++s) {
             const int slot = (((i0 + s) % P) + P) % P;
@@ -221,8 +233,9 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
     };
     load_chunk(k_start + 1);
     settle_chunk(k_start + 1);
-    auto chunk = [&](int b, auto pro) {
-        constexpr int PB = decltype(pro)::value; // prologue chunk index, or -1
+    auto chunk = [&](int b, auto pro, auto no_nan) {
+        constexpr int PB = decltype(pro)::value;  // prologue chunk index, or -1
+        constexpr bool NN = decltype(no_nan)::value; // no norm of the chunk is NaN
         const int k0 = k_start + b * CH;
         // level-0 inputs of the chunk's rows k0+1 .. k0+CH
         float i0h[CH][C], i0v[CH][C], j0h[CH][C], j0v[CH][C];
@@ -304,7 +317,8 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                             nh[c] = proj_atv(qh);
                             nv[c] = proj_atv(qv);
                         } else {
-                            const float sc = iso_scale(norm2_add(0.0f, qh, qv));
+                            const float n2 = norm2_add(0.0f, qh, qv);
+                            const float sc = NN ? iso_scale_no_nan(n2) : iso_scale(n2);
                             nh[c] = qh * sc;
                             nv[c] = qv * sc;
                         }
@@ -377,8 +391,11 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
             }
         }
     };
-    static_for<0, NPRO>([&](auto pb) { chunk(decltype(pb)::value, pb); });
-    for (int b = NPRO; b < nchunk; ++b) chunk(b, std::integral_constant<int, -1>{});
+    static_for<0, NPRO>([&](auto pb) { chunk(decltype(pb)::value, pb, std::false_type{}); });
+    int b = NPRO;
+    if constexpr (TAME)
+        for (; b < nchunk && tame == ~0ull; ++b) chunk(b, std::integral_constant<int, -1>{}, std::true_type{});
+    for (; b < nchunk; ++b) chunk(b, std::integral_constant<int, -1>{}, std::false_type{});
 }
 
 // One pass over every frame: a one-wavefront workgroup per (frame, segment,

@@ -82,9 +82,24 @@ __device__ inline float proj_atv(float q) { return __builtin_amdgcn_fmed3f(q, -1
 
 // Isotropic scale 1 / max(1, sqrt(n2)) = min(1, 1/sqrt(n2)) for a squared norm
 // n2 >= 0. A NaN norm gives 1 (fminf returns its other operand): the finite
-// components of that pixel, with VTV the other frames', stay as they are. The
-// median with 0 and 1 would be the free output clamp of v_rsq_f32 but gives 0.
+// components of that pixel, with VTV the other frames', stay as they are.
 __device__ inline float iso_scale(float n2) { return fminf(1.0f, __builtin_amdgcn_rsqf(n2)); }
+// The same for a norm that is no NaN: the median with 0 and 1 becomes the output
+// clamp of v_rsq_f32 and costs no instruction (fminf is one of the 19 of an
+// ITV2D voxel-iteration), but turns a NaN into 0.
+__device__ inline float iso_scale_no_nan(float n2)
+{
+    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rsqf(n2), 0.0f, 1.0f);
+}
+// A pass that starts from a zero dual meets no NaN norm while every pixel it
+// reads is at most this: |w| <= 3, so |theta| <= |x| + 12 lambda and
+// |q| <= 3 + (|x| + 12 lambda) / (4 lambda) stay finite. One comparison per pixel
+// and pass then saves an instruction per pixel and iteration. (Starting duals
+// would need two to four comparisons more; those passes keep iso_scale.)
+__device__ inline float no_nan_limit(float lam)
+{
+    return lam > 1e-37f && lam < 1e30f ? 1e37f * fminf(1.0f, lam) : -1.0f;
+}
 
 // Semi-implicit (Chambolle 2004) scale 1 / (1 + sqrt(n2)) for the squared
 // norm n2 of z/(8 lambda), with the hardware square root and reciprocal

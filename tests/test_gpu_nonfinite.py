@@ -42,3 +42,25 @@ def test_nonfinite_pixel(tv, B, warm, bad):
             ok = np.isfinite(ref)
             np.testing.assert_allclose(got[ok], ref[ok], rtol=0, atol=2e-5, err_msg=str(kw))
     ctx.close()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("-inf"), 3e38, 1e36, 6e35, 1e30])
+@pytest.mark.parametrize("n", [1, 2, 5, 10])
+def test_huge_pixels_row_passes(n, bad):
+    """The row-pipelined ITV2D passes, which leave a shorter form of the scale
+    where a pixel is not finite or too large for it, against one streaming pass
+    per iteration: the same bits, NaN at the same places."""
+    from paper_2005_08028_amd import scitv
+
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.rand((2, 150, 300), device="cuda", generator=g)
+    for b, i, j in ((0, 20, 150), (0, 75, 60), (1, 130, 220)):
+        X[b, i, j] = bad
+    ctx = scitv.Context(0)
+    want = scitv.sci_tv_denoise(ctx.handle, X, scitv.tv_params(tv="itv2d", lam=0.07, n_inner=n, schedule="stream"))[0]
+    for s in range(1, scitv.sci_tile_shape_count() + 1):
+        if scitv.sci_tile_shape_pipelined(s):
+            prm = scitv.tv_params(tv="itv2d", lam=0.07, n_inner=n, schedule="fused", tile_shape=s, tile_passes=1)
+            got = scitv.sci_tv_denoise(ctx.handle, X, prm)[0]
+            assert torch.allclose(got, want, rtol=0, atol=0, equal_nan=True), s
+    ctx.close()
