@@ -100,8 +100,7 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                                               float *__restrict__ theta_out, float *__restrict__ u_out,
                                               RowRing<M, C> &rr)
 {
-    using D = Dual<DT>;
-    using T = typename D::T;
+    using T = typename Dual<DT>::T;
     constexpr int CH = kRowChunk;
     constexpr int TW = 64 * C;
     constexpr int TXO = TW - 2 * M - 1; // interior columns per strip
@@ -129,6 +128,7 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
         const int cw = lane * C + c;
         off_out[c] = cw >= M + 1 && cw <= TW - 1 - M && j < ny ? (uint32_t)(j - jb) : kNoColumn;
     }
+    static_assert(DT == DT_F32, "16-bit duals run the tiles");
     constexpr uint32_t SZ = (uint32_t)sizeof(T);
 #pragma unroll
     for (int s = 0; s < 2 * P; ++s)
@@ -160,21 +160,21 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
             const uint32_t nv = (uint32_t)i < (uint32_t)(nx - 1) ? ncol : 0u;   // and of p_v
             const RowBuf xb = row_buf(x + rowo, iin ? ncol * 4u : 0u);
 #pragma unroll
-            for (int c = 0; c < C; ++c) xn[s][c] = row_ld<DT_F32>(xb, off_in[c] * 4u);
+            for (int c = 0; c < C; ++c) xn[s][c] = row_ld(xb, off_in[c] * 4u);
             if (MODE >= 1) {
                 const RowBuf hb = row_buf(pc + rowo, nh * SZ), vb = row_buf(pc + (size_t)V + rowo, nv * SZ);
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    lh[s][c] = row_ld<DT>(hb, off_in[c] * SZ);
-                    lv[s][c] = row_ld<DT>(vb, off_in[c] * SZ);
+                    lh[s][c] = row_ld(hb, off_in[c] * SZ);
+                    lv[s][c] = row_ld(vb, off_in[c] * SZ);
                 }
             }
             if (MODE == 2) {
                 const RowBuf hb = row_buf(pp + rowo, nh * SZ), vb = row_buf(pp + (size_t)V + rowo, nv * SZ);
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    mh[s][c] = row_ld<DT>(hb, off_in[c] * SZ);
-                    mv[s][c] = row_ld<DT>(vb, off_in[c] * SZ);
+                    mh[s][c] = row_ld(hb, off_in[c] * SZ);
+                    mv[s][c] = row_ld(vb, off_in[c] * SZ);
                 }
             }
         }
@@ -375,8 +375,8 @@ __device__ __forceinline__ void fgp_rows_body(int nx, int ny, int sx, int seg, i
                     const RowBuf vb = row_buf(out + (size_t)V + rowo, ncol * SZ);
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        row_st(hb, off_out[c] * SZ, D::to(h[c]));
-                        row_st(vb, off_out[c] * SZ, D::to(v[c]));
+                        row_st(hb, off_out[c] * SZ, h[c]);
+                        row_st(vb, off_out[c] * SZ, v[c]);
                     }
                 };
                 if (theta_out) put(theta_out, th);

@@ -140,25 +140,13 @@ template <typename T> __device__ inline RowBuf row_buf(const T *row, uint32_t by
 {
     return __builtin_amdgcn_make_buffer_rsrc((void *)const_cast<T *>(row), 0, (int)bytes, 0x00020000);
 }
-template <int DT> __device__ inline float row_ld(RowBuf b, uint32_t off)
+__device__ inline float row_ld(RowBuf b, uint32_t off)
 {
-    using T = typename Dual<DT>::T;
-    if constexpr (DT == DT_F32)
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
-    else
-        return Dual<DT>::cvt(__builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(b, (int)off, 0, 0)));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
 }
 __device__ inline void row_st(RowBuf b, uint32_t off, float v)
 {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)off, 0, 0);
-}
-__device__ inline void row_st(RowBuf b, uint32_t off, uint16_t v)
-{
-    __builtin_amdgcn_raw_buffer_store_b16(v, b, (int)off, 0, 0);
-}
-__device__ inline void row_st(RowBuf b, uint32_t off, _Float16 v)
-{
-    row_st(b, off, __builtin_bit_cast(uint16_t, v));
 }
 
 // Keep a prefetch where it stands: memory reads above cannot sink below (the

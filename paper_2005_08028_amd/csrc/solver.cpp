@@ -234,7 +234,7 @@ double call_us(const sci_ctx *ctx, const sci_tv_params &p, const sci_dims &d, in
 
 // Tile shape and number of passes of the fused schedule: explicit
 // (tile_shape / tile_passes >= 1), else the autotuned choice for this problem,
-// else the pair with the smallest estimate of at most three passes more than
+// else the pair with the smallest estimate of at most two passes more than
 // needed. Every choice gives the same bits with float32 duals. 16-bit duals
 // are rounded between passes, so their split is fixed: one pass for a cold
 // call of at most kTileMaxM iterations whose dual is not kept when the
