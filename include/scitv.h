@@ -115,8 +115,9 @@ typedef struct {
                                 bits; passes that touch 16-bit duals run shape 1); k >= 1 = shape k
                                 (see sci_tile_shape_info) */
     int32_t tile_passes;     /* fused schedule: passes over HBM per denoiser call (each runs about
-                                n_inner / tile_passes iterations, at most 10); 0 = autotuned or
-                                default (chosen with the shape; passes of about 5 iterations where
+                                n_inner / tile_passes iterations, at most 10; ATV and ITV2D: not for
+                                the check intervals of gap_tol > 0, which run in the fewest passes);
+                                0 = autotuned or default (chosen with the shape; passes of about 5 iterations where
                                 16-bit duals are rounded between them; VTV: the fewest passes its
                                 kernel runs) */
     int32_t chambolle04;     /* 1 = Chambolle's (2004) semi-implicit step (Sec. 2.3):

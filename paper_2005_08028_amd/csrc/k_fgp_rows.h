@@ -32,9 +32,10 @@
 // bit-identical to theirs with float32 dual storage.
 //
 // What bounds it: vector instruction issue (17 per voxel-iteration for ITV2D,
-// v_rsq_f32 taking two slots), two wavefronts per SIMD. For a cold
-// 10-iteration ITV2D pass at 1024x1024x24 (128-row segments, 1,920
-// wavefronts), three things brought it there from 189 us:
+// v_rsq_f32 taking two slots), two wavefronts per SIMD. A cold 10-iteration
+// ITV2D pass at 1024x1024x24 (128-row segments, 1,920 wavefronts) takes 169 us;
+// three things brought it there from 189 us (their figures without the case of
+// a NaN norm, which adds 3 us):
 //   * The SIMD serves the older of its two wavefronts first. That one then
 //     runs as if alone (119 us) and the other is left to finish alone (185
 //     us), with the vector unit 70 % busy to the end. A priority that falls

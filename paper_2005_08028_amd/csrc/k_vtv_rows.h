@@ -23,8 +23,9 @@
 // Levels the pipeline fill has not reached are left out of the first chunks
 // at compile time, as in the 2D kernel.
 //
-// What bounds it: the latency of the exchanges; a wavefront waits 37 % of its
-// time and the vector unit is 55 % to 70 % busy. Raising the priority of a
+// What bounds it: the latency of the exchanges; a wavefront of the two passes
+// at 1024x1024x24 waits 35 % and 37 % of its time, and the vector unit is 73 %
+// and 59 % busy with the two of a SIMD. Raising the priority of a
 // wavefront that is on its way to an exchange's barrier took passes of 5 from
 // 30.9 to 27.8 us at 512x512x10 and from 151 + 222 to 148 + 216 us at
 // 1024x1024x24 (cold, and from the records); two barriers per round, one for
@@ -96,15 +97,15 @@ enum class VtvForm { kFull, kQuiet, kLean };
 
 // The form of a kernel, by its registers. Four wavefronts per SIMD (at most 128)
 // hold the two workgroups per CU that the segment height counts on; with three
-// (at most 168) two of 5 or 6 wavefronts count as resident but run one after
-// the other, two of 7 or 8 do not count. 512x512, microseconds in the full
+// (at most 168) two of 5 or 6 wavefronts count as resident but take the time of
+// one after the other, two of 7 or 8 do not count. 512x512, microseconds in the full
 // or quiet form -> in the form chosen: warm 5 of B = 9 in bf16 (136 -> 128
 // registers) 49.5 -> 31.2, of B = 16 43.7 -> 39.2; warm Chambolle-2004 5 of B = 9
 // (133 -> 127) 48.0 -> 33.7; cold 2 of B = 25 (130 -> 126) 24.6 -> 22.7. Registers
 // grow with M + MODE by about 6.5 per frame, so with two frames 128 lies at 6,
 // with four at 2; there the kernels that cross it take the richest form that
-// does not. The 168 line needs no such care: below it 5 or 6 wavefronts run one
-// workgroup at a time on segments cut for two (warm 8 of B = 9: 84 us at 168
+// does not. The 168 line needs no such care: crossing it cuts the segments of 5
+// or 6 wavefronts for one workgroup per CU (warm 8 of B = 9: 84 us at 168
 // registers, 60 at 170).
 constexpr VtvForm vtv_form(int m, int kf, int mode, int ch_step, int dt, int qio, int ns)
 {
